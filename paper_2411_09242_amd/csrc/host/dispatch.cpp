@@ -429,9 +429,8 @@ NodeKernel prepare_gemm(const Node& nd, int variant, int dtype, const std::vecto
   // 256x128 with a three-stage ring, two workgroups per CU, 9: 128x128
   // persistent with the whole K (at most 128) in LDS;
   // fp32 6: 16x32 with K split over 8 wavefronts, 7: 32x32 over 4, operands
-  // loaded straight into MFMA registers, 8 and 9: 128x128 double-buffered
-  // in LDS with the next K-tile in flight in registers, over sixteen or
-  // eight wavefronts
+  // loaded straight into MFMA registers, 8: 256x128 and 9: 128x128, bf16
+  // splits (k_gemm_f32_split.hip)
   static const uint32_t TM[] = {128, 64, 32, 32, 64, 32, 256, 128, 256, 128};
   static const uint32_t TN[] = {128, 64, 32, 32, 32, 32, 128, 128, 128, 128};
   uint32_t tm = TM[tile], tn = TN[tile];
@@ -447,8 +446,9 @@ NodeKernel prepare_gemm(const Node& nd, int variant, int dtype, const std::vecto
     return k;
   }
   if (tile >= 6 && f32) {
-    tm = tile == 6 ? 16 : tile == 7 ? 32 : 128;
-    tn = tile >= 8 ? 128 : 32;
+    static const uint32_t FM[] = {16, 32, 256, 128}, FN[] = {32, 32, 128, 128};
+    tm = FM[tile - 6];
+    tn = FN[tile - 6];
     if ((k.amode != GM_K && k.amode != GM_MN) || (k.bmode != GM_K && k.bmode != GM_MN)) {
       k.available = false;
       k.why = "the direct-load tiles need unit-stride K or M/N operands";
@@ -625,7 +625,7 @@ std::string NodeKernel::name() const {
         return e.empty() ? e : "_e" + e;
       };
       static const char* tiles[] = {"t128", "t64", "sk32w4", "sk32w8", "sk64x32w4", "sk32w16", "p256x128", "p128", "p256x128s3", "q128"};
-      static const char* tiles_f32[] = {"t128", "t64", "sk32w4", "sk32w8", "sk64x32w4", "sk32w16", "dl16x32w8", "dl32w4", "r128", "r128w8"};
+      static const char* tiles_f32[] = {"t128", "t64", "sk32w4", "sk32w8", "sk64x32w4", "sk32w16", "dl16x32w8", "dl32w4", "s256x128", "s128"};
       return "gemm_" + dt + "_" + (dtype == DT_BF16 ? tiles : tiles_f32)[gemm_tile] + "_a" + gm[amode] + "_b" + gm[bmode] + "_c" +
              (cmode == 1 ? "n" : cmode == 2 ? "m" : "g") + (gemm.causal ? "_causal" + std::to_string(gemm.causal) : "") +
              epi_suffix();

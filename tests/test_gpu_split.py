@@ -1,0 +1,108 @@
+"""GPU tests of the fp32 GEMM tiles that multiply three-way bf16 splits
+(MatMul variants 8, 9 and, on packed weights, 18, 19): tile edges and K-tile
+remainders in every operand orientation, the error against 64-bit arithmetic
+beside the fp32 MFMA tile's, and infinities, NaN and the largest floats."""
+from __future__ import annotations
+
+import itertools
+
+import numpy as np
+import pytest
+
+from gpu_util import say
+from oracle import layouts
+from test_gpu_ops import _check_gemm, proj_graph
+
+pytestmark = pytest.mark.gpu
+
+VARIANTS = [8, 9, 18, 19]
+
+
+def product(variant, x, w):
+    """x @ w by one MatMul variant (row-major operands and result)."""
+    import json
+    import tempfile
+
+    import torch
+    from paper_2411_09242_amd import fluid as F
+    (M, K), N = x.shape, w.shape[1]
+    g = F.Graph.from_desc(dict(dtype="f32", inputs=[[M, K]], consts=[dict(role="weight", shape=[K, N], dtype="f32")],
+                               nodes=[dict(op="matmul", ins=[0, ~0], out_shape=[M, N])], outputs=[1]))
+    cost = [1 if v == variant else -1 for v in range(20)]
+    table = {"format": "fluid-cost-table/1", "edges": [[[0, 1]], [[0, 1]]], "node_sig": [0],
+             "sigs": [{"op": "matmul", "in_shapes": [[M, K]], "out_shape": [M, N],
+                       "entries": [[[[0, 1]], [0, 1], cost]]}]}
+    with tempfile.NamedTemporaryFile("w", suffix=".json") as f:
+        json.dump(table, f)
+        f.flush()
+        t = F.CostTable.load(f.name, g)
+    lp = F.LayoutPlan(g, t)
+    ex = F.Executor(g, lp, F.ArenaPlan(g, lp), [w], [x])
+    y = ex.run()[0]
+    torch.cuda.synchronize()
+    return y.cpu().numpy()
+
+
+@pytest.mark.parametrize("shape", [(1, 4, 4, 4), (1, 257, 68, 132), (3, 43, 36, 260), (1, 128, 96, 128)], ids=str)
+@pytest.mark.parametrize("variant", VARIANTS)
+def test_split_tile_edges(shape, variant, tmp_path):
+    """One element past a tile, K not a multiple of a K-tile, exact tiles;
+    A and C in every layout."""
+    B, S, K, N = shape
+    og, a, c = proj_graph(B, S, K, N, "f32")
+    for pa, pc in itertools.product(layouts.layout_list((B, S, K)), layouts.layout_list((B, S, N))):
+        say(f"split {shape} v{variant} A{pa} C{pc}")
+        _check_gemm(og, {a: pa, c: pc}, {1: variant}, tmp_path, S + K, "f32")
+
+
+@pytest.mark.parametrize("dist", ["normal", "positive", "wide"])
+@pytest.mark.parametrize("variant", VARIANTS)
+def test_split_error(dist, variant):
+    """Every element within the bound of any fp32 summation, (K + 1) 2^-24
+    sum |a b|; the root mean square of the errors in units of sum |a b| no
+    larger than the 64 x 64 fp32 MFMA tile's, for values spread over ten
+    decades ("wide") too."""
+    rng = np.random.default_rng(7)
+    M, K, N = 200, 1024, 136
+    x, w = rng.standard_normal((M, K)), 0.02 * rng.standard_normal((K, N))
+    if dist == "positive":
+        x, w = np.abs(x), np.abs(w)
+    elif dist == "wide":
+        x, w = x * np.exp(4 * rng.standard_normal((M, K))), w * np.exp(4 * rng.standard_normal((K, N)))
+    x, w = x.astype(np.float32), w.astype(np.float32)
+    exact = x.astype(np.float64) @ w.astype(np.float64)
+    size = np.abs(x).astype(np.float64) @ np.abs(w)
+    err = {v: (product(v, x, w) - exact) / size for v in (variant, 1)}
+    assert (np.abs(err[variant]) <= (K + 1) * 2.0 ** -24).all()
+    rms = {v: float(np.sqrt((e * e).mean())) for v, e in err.items()}
+    say(dist, variant, rms)
+    assert rms[variant] <= rms[1]
+
+
+@pytest.mark.parametrize("variant", VARIANTS)
+def test_split_exceptions(variant):
+    """Infinities, NaN, values that round to a bf16 infinity and overflowing
+    sums give what fp32 arithmetic gives, and leave other tiles alone."""
+    rng = np.random.default_rng(8)
+    M, K, N = 300, 64, 264
+    x, w = rng.standard_normal((M, K)).astype(np.float32), rng.standard_normal((K, N)).astype(np.float32)
+    big = np.float32(3.4e38)
+    x[3, 5], w[5, 2] = np.inf, 0.0            # inf * 0: NaN in column 2
+    w[5, 4] = 1.0                             # inf * 1 (exact in bf16): inf
+    x[7, 9], w[9] = big, 0.5 * np.sign(w[9])  # rounds to a bf16 infinity, the product is finite
+    x[60, 1] = np.nan
+    w[8, 20] = -np.inf
+    x[9, 8] = 0.0
+    w[10:12] = 0.25
+    x[20, 10], x[20, 11], w[10:12, 3] = big, big, 1.0   # overflows in column 3 alone
+    got = product(variant, x, w)
+    with np.errstate(all="ignore"):
+        ref = x.astype(np.float64) @ w.astype(np.float64)
+        ref = np.where(np.abs(ref) > np.finfo(np.float32).max, np.sign(ref) * np.inf, ref)
+    assert (np.isnan(got) == np.isnan(ref)).all()
+    inf = np.isinf(ref)
+    assert (got[inf] == ref[inf]).all() and np.isfinite(got[np.isfinite(ref)]).all()
+    ok = np.isfinite(ref)
+    bound = (K + 1) * 2.0 ** -24 * (np.abs(np.nan_to_num(x, posinf=0)).astype(np.float64) @
+                                    np.abs(np.nan_to_num(w, neginf=0)))
+    assert (np.abs(got - ref)[ok] <= bound[ok]).all()
