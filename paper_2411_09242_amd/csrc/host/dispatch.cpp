@@ -429,7 +429,7 @@ NodeKernel prepare_gemm(const Node& nd, int variant, int dtype, const std::vecto
   // 256x128 with a three-stage ring, two workgroups per CU, 9: 128x128
   // persistent with the whole K (at most 128) in LDS;
   // fp32 6: 16x32 with K split over 8 wavefronts, 7: 32x32 over 4, operands
-  // loaded straight into MFMA registers, 8: 256x128 and 9: 128x128, bf16
+  // by LDS DMA per wavefront, 8: 256x128 and 9: 128x128, bf16
   // splits (k_gemm_f32_split.hip)
   static const uint32_t TM[] = {128, 64, 32, 32, 64, 32, 256, 128, 256, 128};
   static const uint32_t TN[] = {128, 64, 32, 32, 32, 32, 128, 128, 128, 128};

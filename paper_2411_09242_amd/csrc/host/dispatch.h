@@ -9,8 +9,8 @@
 //                               bf16 6: 256x128, 7: 128x128 tile, loads K
 //                               tiles ahead; 8: 256x128, two workgroups per
 //                               CU; 9: 128x128, whole K (<= 128) in LDS;
-//                               fp32 6: 16x32, 7: 32x32 tiles, operands
-//                               straight into registers; 8: 256x128, 9:
+//                               fp32 6: 16x32, 7: 32x32 tiles, operands by
+//                               LDS DMA per wavefront; 8: 256x128, 9:
 //                               128x128, three-way bf16 splits on the bf16
 //                               matrix cores
 //   ADD MUL                     0: streaming elementwise in output order
