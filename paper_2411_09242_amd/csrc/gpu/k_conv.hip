@@ -8,12 +8,9 @@
 // sits at row_offset(m) + col_offset(k) with row_offset = n*sN + i*sH + j*sW
 // and col_offset = c*sC + u*sH + v*sW, so the unfolded input matrix is never
 // built: each thread keeps the row offsets of its pixels and forms column
-// offsets per K-tile.  Two load orders:
-//   KORD 0: k = (c, u, v) (the weight's row-major order); a wavefront loads
-//           64 consecutive pixels of one k -- coalesced when W is the
-//           input's unit-stride dim (NCHW-like layouts);
-//   KORD 1: k = (u, v, c); a wavefront loads 16 consecutive k of 4 pixels --
-//           coalesced when C is unit-stride (NHWC-like layouts).
+// offsets per K-tile.  k = (u, v, c): a wavefront loads 16 consecutive k of
+// 4 pixels -- coalesced when C is unit-stride (NHWC-like layouts; the other
+// order, and the faster arithmetic: k_conv_split.hip).
 // A 64 x 64 output tile per group of 256 threads (4 wavefronts, 2 x 2, each
 // 32 x 32 -- or a 32 x 32 tile per single-wavefront group -- with
 // v_mfma_f32_32x32x2_f32: lane l reads A[l%32][l/32] and
@@ -33,25 +30,16 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-template <int KORD>
 __device__ __forceinline__ int32_t conv_col_off(const ConvParams& p, uint32_t k, int32_t* waddr) {
-  uint32_t c, u, v;
-  if constexpr (KORD == 0) {
-    c = fdiv(k, p.khw_div);
-    const uint32_t r = k - c * p.KHW;
-    u = fdiv(r, p.kw_div);
-    v = r - u * p.KW;
-  } else {
-    u = fdiv(k, p.kwc_div);
-    const uint32_t r = k - u * p.KWC;
-    v = fdiv(r, p.c_div);
-    c = r - v * p.C;
-  }
+  const uint32_t u = fdiv(k, p.kwc_div);
+  const uint32_t r = k - u * p.KWC;
+  const uint32_t v = fdiv(r, p.c_div);
+  const uint32_t c = r - v * p.C;
   *waddr = (int32_t)(c * p.KHW + u * p.KW + v);
   return (int32_t)c * p.x_c + (int32_t)u * p.x_h + (int32_t)v * p.x_w;
 }
 
-template <int KORD, int KS, int TW>
+template <int KS, int TW>
 __global__ __launch_bounds__(64 * (TW / 32) * (TW / 32) * KS) void conv_f32_kernel(ConvParams p) {
   // TW x TW output tile per group of WPG wavefronts ((TW/32)^2, each a
   // 32 x 32 block); NT threads per group
@@ -81,20 +69,15 @@ __global__ __launch_bounds__(64 * (TW / 32) * (TW / 32) * KS) void conv_f32_kern
   };
 
   // A: AE elements per thread per K-tile; element r of thread t is index
-  // t + NT r of the tile, pixel-fastest (KORD 0) or k-fastest (KORD 1)
+  // t + NT r of the tile, k-fastest
   int a_m[AE], a_k[AE];
   int32_t a_off[AE];
   bool a_ok[AE];
 #pragma unroll
   for (int r = 0; r < AE; ++r) {
     const int idx = tid + NT * r;
-    if constexpr (KORD == 0) {
-      a_m[r] = idx % BM;
-      a_k[r] = idx / BM;
-    } else {
-      a_k[r] = idx % BK;
-      a_m[r] = idx / BK;
-    }
+    a_k[r] = idx % BK;
+    a_m[r] = idx / BK;
     const uint32_t m = m0 + a_m[r];
     a_ok[r] = m < p.M;
     a_off[r] = a_ok[r] ? row_off(m, p.x_n, p.x_h, p.x_w) : 0;
@@ -112,27 +95,18 @@ __global__ __launch_bounds__(64 * (TW / 32) * (TW / 32) * KS) void conv_f32_kern
 
   float ra[AE], rb[BE];
   auto gload = [&](uint32_t k0) {
-    if constexpr (KORD == 0) {
-      // per element its own k
-#pragma unroll
-      for (int r = 0; r < AE; ++r) {
-        const uint32_t k = k0 + a_k[r];
-        int32_t wa;
-        const int32_t co = k < p.K ? conv_col_off<0>(p, k, &wa) : 0;
-        ra[r] = (a_ok[r] && k < p.K) ? p.x[a_off[r] + co] : 0.f;
-      }
-    } else {
+    {
       // one k per thread (NT is a multiple of BK), several pixels
       const uint32_t k = k0 + a_k[0];
       int32_t wa;
-      const int32_t co = k < p.K ? conv_col_off<1>(p, k, &wa) : 0;
+      const int32_t co = k < p.K ? conv_col_off(p, k, &wa) : 0;
 #pragma unroll
       for (int r = 0; r < AE; ++r) ra[r] = (a_ok[r] && k < p.K) ? p.x[a_off[r] + co] : 0.f;
     }
     {
       const uint32_t k = k0 + b_k[0];
       int32_t wa = 0;
-      if (k < p.K) (void)conv_col_off<KORD>(p, k, &wa);
+      if (k < p.K) (void)conv_col_off(p, k, &wa);
 #pragma unroll
       for (int r = 0; r < BE; ++r)
         rb[r] = (b_ok[r] && k < p.K) ? p.w[(int32_t)(n0 + b_n[r]) * (int32_t)p.K + wa] : 0.f;
@@ -195,23 +169,16 @@ __global__ __launch_bounds__(64 * (TW / 32) * (TW / 32) * KS) void conv_f32_kern
 }  // namespace
 
 hipError_t launch_conv(const NodeKernel& k, hipStream_t s) {
+  if (k.conv_bm) return launch_conv_split(k, s);
   const ConvParams& p = k.conv;
   const uint32_t tw = k.conv_tile;
   const uint32_t grid = ((p.M + tw - 1) / tw) * p.tiles_n;
-#define FLUID_CONV(KO, KSv, TWv) \
-  hipLaunchKernelGGL((conv_f32_kernel<KO, KSv, TWv>), dim3(grid), dim3(64 * (TWv / 32) * (TWv / 32) * KSv), 0, s, p)
-  if (tw == 64 && k.conv_ks == 1) {
-    if (k.conv_kord == 0) FLUID_CONV(0, 1, 64);
-    else FLUID_CONV(1, 1, 64);
-  } else if (tw == 64 && k.conv_ks == 4) {
-    if (k.conv_kord == 0) FLUID_CONV(0, 4, 64);
-    else FLUID_CONV(1, 4, 64);
-  } else if (tw == 32 && k.conv_ks == 8) {
-    if (k.conv_kord == 0) FLUID_CONV(0, 8, 32);
-    else FLUID_CONV(1, 8, 32);
-  } else {
-    return hipErrorInvalidValue;
-  }
+#define FLUID_CONV(KSv, TWv) \
+  hipLaunchKernelGGL((conv_f32_kernel<KSv, TWv>), dim3(grid), dim3(64 * (TWv / 32) * (TWv / 32) * KSv), 0, s, p)
+  if (tw == 64 && k.conv_ks == 1) FLUID_CONV(1, 64);
+  else if (tw == 64 && k.conv_ks == 4) FLUID_CONV(4, 64);
+  else if (tw == 32 && k.conv_ks == 8) FLUID_CONV(8, 32);
+  else return hipErrorInvalidValue;
 #undef FLUID_CONV
   return hipGetLastError();
 }

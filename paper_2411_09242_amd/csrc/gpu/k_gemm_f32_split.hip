@@ -16,42 +16,12 @@
 // one recomputes its tile with the fp32 MFMA straight from memory, so that
 // infinities, NaN and values up to the largest float behave as in fp32.
 // (An l below 2^-126 loses bits: relevant for |x| below 2^-108.)
-#include "gemm_common.h"
 #include "launch.h"
+#include "split_common.h"
 
 namespace fluid {
 
 namespace {
-
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-
-// Two floats to one dword of bf16 (round to nearest even).
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-  const f32x2 v = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
-// The three bf16 parts of the pair (a, b): plane 0 the leading parts.
-__device__ __forceinline__ void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
-  h = pack_bf16(a, b);
-  a -= __uint_as_float(h << 16);
-  b -= __uint_as_float(h & 0xffff0000u);
-  m = pack_bf16(a, b);
-  a -= __uint_as_float(m << 16);
-  b -= __uint_as_float(m & 0xffff0000u);
-  l = pack_bf16(a, b);
-}
-
-__device__ __forceinline__ float bload4(Rsrc r, uint32_t off) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-}
-
-// Chunk position of the 16-byte chunk c (8 k) of row r: 64-byte rows
-// (32 k) as in the bf16 DMA tile, 128-byte rows (64 k) by r % 8.
-template <int BK>
-__device__ __forceinline__ int split_swz(int r) {
-  return BK == 32 ? (((r >> 1) ^ (r >> 3)) & 3) : (r & 7);
-}
 
 // Tile of workgroup b: the tiles are dealt to the eight XCDs (b % 8) in
 // contiguous ranges, walked within a batch in bands of four tile rows, so

@@ -22,6 +22,7 @@ hipError_t launch_gemm_f32_dl_group(const NodeKernel& k, const GemmGroup& G, hip
 hipError_t launch_fill(void* p, uint64_t bytes, uint32_t seed, hipStream_t s);
 hipError_t launch_window(const NodeKernel& k, hipStream_t s);
 hipError_t launch_conv(const NodeKernel& k, hipStream_t s);
+hipError_t launch_conv_split(const NodeKernel& k, hipStream_t s);
 
 inline hipError_t launch_node_kernel(const NodeKernel& k, hipStream_t s) {
   switch (k.family) {

@@ -499,11 +499,14 @@ NodeKernel prepare_window(const Node& nd, int dtype, const std::vector<Operand>&
   return k;
 }
 
-// Conv: variant 0 reduces over (c, u, v) with wavefronts along pixels, 1
-// over (u, v, c) with wavefronts along channels; variants 2 and 3 are 0 and
-// 1 with the K-tiles of a tile split over 4 groups of wavefronts in one
-// workgroup; variants 4 and 5 take 32 x 32 tiles with the K-tiles split
-// over 8 single-wavefront groups (k_conv.hip).
+// Conv: the odd variants reduce over (u, v, c) on the fp32 MFMA, wavefronts
+// along channels (k_conv.hip): 1 with 64 x 64 tiles, 3 the same with the
+// K-tiles of a tile split over 4 groups of wavefronts in one workgroup, 5
+// with 32 x 32 tiles and 8 single-wavefront groups.  The even ones reduce
+// over (c, u, v) in bf16 splits, wavefronts along pixels
+// (k_conv_split.hip): 0 with 128 x 64 tiles, 2 with 64 x 64, 4 with 64 x 32.
+// Those address their operands by buffer loads; for a tensor of 2 GiB or
+// more they run the fp32 kernel after them.
 NodeKernel prepare_conv(const Node& nd, int variant, int dtype, const std::vector<Operand>& ins, const Operand& out) {
   NodeKernel k;
   k.family = KF_CONV;
@@ -541,9 +544,18 @@ NodeKernel prepare_conv(const Node& nd, int variant, int dtype, const std::vecto
   p.x_n = (int32_t)x.stride[0]; p.x_c = (int32_t)x.stride[1]; p.x_h = (int32_t)x.stride[2]; p.x_w = (int32_t)x.stride[3];
   p.y_n = (int32_t)out.stride[0]; p.y_c = (int32_t)out.stride[1]; p.y_h = (int32_t)out.stride[2];
   p.y_w = (int32_t)out.stride[3];
-  k.conv_kord = variant & 1;
-  k.conv_ks = variant >= 4 ? 8 : variant >= 2 ? 4 : 1;
+  const int64_t xb = 4 * numel(x.shape), wb = 4 * numel(w.shape);
+  const bool split = variant % 2 == 0 && xb < 0x7fffffff && wb < 0x7fffffff;
+  p.x_bytes = (uint32_t)std::min<int64_t>(xb, 0x7fffffff);
+  p.w_bytes = (uint32_t)std::min<int64_t>(wb, 0x7fffffff);
+  k.conv_kord = split ? 0 : 1;
   k.conv_tile = variant >= 4 ? 32 : 64;
+  if (split) {
+    k.conv_bm = variant == 0 ? 128 : 64;
+    k.conv_ks = variant == 4 ? 8 : 4;
+  } else {
+    k.conv_ks = variant >= 4 ? 8 : variant >= 2 ? 4 : 1;
+  }
   p.tiles_n = (p.Co + k.conv_tile - 1) / k.conv_tile;
   k.available = true;
   return k;
@@ -615,7 +627,7 @@ std::string NodeKernel::name() const {
     case KF_RED_COL: return std::string(red_names[red.op]) + "_col_" + dt;
     case KF_WIN: return std::string(win.op == 0 ? "pad_" : "maxpool_") + dt;
     case KF_CONV:
-      return "conv_" + dt + "_t" + std::to_string(conv_tile) + (conv_kord == 0 ? "_kcuv" : "_kuvc") +
+      return "conv_" + dt + (conv_bm ? "_s" + std::to_string(conv_bm) + "x" : "_t") + std::to_string(conv_tile) + (conv_kord == 0 ? "_kcuv" : "_kuvc") +
              (conv_ks > 1 ? "_ks" + std::to_string(conv_ks) : "");
     case KF_GEMM: {
       // fused epilogue steps: b bias, g GELU, s SiLU, a / m Add / Mul of R

@@ -108,8 +108,8 @@ struct WinParams {
 
 // Convolution (no padding, stride 1) as an implicit GEMM: row m = (n, i, j)
 // an output pixel, column o an output channel, reduction index k over
-// (c, u, v) -- in the weight's row-major order (KORD 0) or as (u, v, c)
-// (KORD 1, channel fastest) -- so that x[n, c, i+u, j+v] sits at
+// (c, u, v) -- in the weight's row-major order (k_conv_split.hip) or as
+// (u, v, c), channel fastest (k_conv.hip) -- so that x[n, c, i+u, j+v] sits at
 // row_offset(m) + col_offset(k) for any layout of x.
 struct ConvParams {
   const float* x;
@@ -122,6 +122,7 @@ struct ConvParams {
   int32_t x_n, x_c, x_h, x_w;
   int32_t y_n, y_c, y_h, y_w;
   uint32_t tiles_n;
+  uint32_t x_bytes, w_bytes;  // tensor sizes (the bf16-split kernel: below 2 GiB)
 };
 
 // C[g, m, n] = sum_k A[g, m, k] * B[g, k, n]; g = g1 * G2 + g2 and

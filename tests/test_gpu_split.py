@@ -106,3 +106,63 @@ def test_split_exceptions(variant):
     bound = (K + 1) * 2.0 ** -24 * (np.abs(np.nan_to_num(x, posinf=0)).astype(np.float64) @
                                     np.abs(np.nan_to_num(w, neginf=0)))
     assert (np.abs(got - ref)[ok] <= bound[ok]).all()
+
+
+# (x, Co, kernel): one pixel and one channel past a tile, K not a multiple of
+# four (4-byte weight loads), a K-tile more than the pipeline holds, two images
+CONVS = [((1, 3, 10, 9), 65, 3), ((2, 5, 9, 11), 33, 2), ((1, 40, 12, 12), 64, 3), ((1, 130, 5, 5), 31, 1)]
+
+
+def convolution(variant, x, w, b):
+    import json
+    import tempfile
+
+    import torch
+    from paper_2411_09242_amd import fluid as F
+    out = [x.shape[0], w.shape[0], x.shape[2] - w.shape[2] + 1, x.shape[3] - w.shape[3] + 1]
+    eye = [0, 1, 2, 3]
+    g = F.Graph.from_desc(dict(dtype="f32", inputs=[list(x.shape)],
+                               consts=[dict(role="weight", shape=list(w.shape), dtype="f32"),
+                                       dict(role="bias", shape=list(b.shape), dtype="f32")],
+                               nodes=[dict(op="conv", ins=[0, ~0, ~1], out_shape=out)], outputs=[1]))
+    table = {"format": "fluid-cost-table/1", "edges": [[eye], [eye]], "node_sig": [0],
+             "sigs": [{"op": "conv", "in_shapes": [list(x.shape)], "out_shape": out,
+                       "entries": [[[eye], eye, [1 if v == variant else -1 for v in range(6)]]]}]}
+    with tempfile.NamedTemporaryFile("w", suffix=".json") as f:
+        json.dump(table, f)
+        f.flush()
+        t = F.CostTable.load(f.name, g)
+    lp = F.LayoutPlan(g, t)
+    ex = F.Executor(g, lp, F.ArenaPlan(g, lp), [w, b], [x])
+    y = ex.run()[0]
+    torch.cuda.synchronize()
+    return y.cpu().numpy()
+
+
+@pytest.mark.parametrize("case", CONVS, ids=str)
+@pytest.mark.parametrize("variant", [0, 2, 4])
+def test_split_convolution(case, variant):
+    """Every output within (K + 2) 2^-24 of its sum |x w| + |b|, the bound of
+    any fp32 summation; an infinite and a huge input give what fp32 gives."""
+    from numpy.lib.stride_tricks import sliding_window_view
+    shape, Co, k = case
+    rng = np.random.default_rng(Co)
+    x = rng.standard_normal(shape).astype(np.float32)
+    w = rng.standard_normal((Co, shape[1], k, k)).astype(np.float32)
+    b = rng.standard_normal(Co).astype(np.float32)
+
+    def exact(x, w):
+        win = sliding_window_view(x.astype(np.float64), (k, k), axis=(2, 3))
+        with np.errstate(all="ignore"):
+            return np.einsum("nchwuv,ocuv->nohw", win, w.astype(np.float64))
+
+    ref = exact(x, w) + b[:, None, None]
+    bound = (shape[1] * k * k + 2) * 2.0 ** -24 * (exact(np.abs(x), np.abs(w)) + np.abs(b)[:, None, None])
+    say("conv", case, variant)
+    assert (np.abs(convolution(variant, x, w, b) - ref) <= bound).all()
+    x[0, 1, 2, 2], x[0, 2, -1, -1] = np.inf, 3.4e38
+    w *= np.float32(2.0 ** -4) * (np.abs(w) < 3)
+    ref = exact(x, w) + b[:, None, None]
+    got = convolution(variant, x, w, b)
+    assert (np.isnan(got) == np.isnan(ref)).all() and (got[np.isinf(ref)] == ref[np.isinf(ref)]).all()
+    assert np.isfinite(got[np.isfinite(ref)]).all()
