@@ -10,10 +10,11 @@
 //  * row, a workgroup per row (variant 2; 16-byte pieces only): four times
 //    the wavefronts per row, a quarter of the pieces each, sums through LDS
 //    -- for long rows and few of them; the cost table decides per shape.
-//  * column (variant 1): one lane per row, consecutive lanes on consecutive
-//    rows, so a layout whose unit-stride dim is a row dim still reads and
-//    writes coalesced; the row is streamed twice (three times for
-//    LayerNorm's exact two-pass variance).
+//  * column (variant 1): neighbouring lanes on neighbouring rows, so a layout
+//    whose unit-stride dim is a row dim still reads and writes coalesced; the
+//    row is held in the registers of 16 wavefronts (red_colb_kernel) up to
+//    8192 values, a longer one is streamed by one lane, twice (three times
+//    for LayerNorm's exact two-pass variance).
 // Causal softmax: keys k > q (q = index along the second-to-last logical
 // dim) get probability exactly 0.  The RED_SUM_* norms read a second
 // tensor x1 (own layout) and normalise x + x1, the sum formed on load (a
@@ -64,6 +65,18 @@ __global__ __launch_bounds__(256) void red_row_kernel(RedParams p) {
   row_offsets(p, row, io, oo, io1, qi);
   const uint32_t R = p.R;
   const uint32_t valid = (OP == RED_SOFTMAX && p.causal) ? min(R, qi + 1u) : R;
+  // gamma and beta are fetched with the row, not after the reduction, where
+  // they fit the registers
+  constexpr bool PRE = OP != RED_SOFTMAX && NPL <= 16;
+  float gv[PRE ? NPL : 1], bv[PRE && BOP == RED_LAYERNORM ? NPL : 1];
+  if constexpr (PRE) {
+#pragma unroll
+    for (int j = 0; j < NPL; ++j) {
+      const uint32_t kc = min((uint32_t)lane + 64u * j, R - 1u);
+      gv[j] = Elem<T>::load(p.gamma, kc);
+      if constexpr (BOP == RED_LAYERNORM) bv[j] = Elem<T>::load(p.beta, kc);
+    }
+  }
   float v[NPL];
 #pragma unroll
   for (int j = 0; j < NPL; ++j) {
@@ -129,8 +142,8 @@ __global__ __launch_bounds__(256) void red_row_kernel(RedParams p) {
     for (int j = 0; j < NPL; ++j) {
       const uint32_t k = (uint32_t)lane + 64u * j;
       if (k < R) {
-        float y = (v[j] - mean) * rstd * Elem<T>::load(p.gamma, k);
-        if constexpr (BOP == RED_LAYERNORM) y += Elem<T>::load(p.beta, k);
+        float y = (v[j] - mean) * rstd * (PRE ? gv[PRE ? j : 0] : Elem<T>::load(p.gamma, k));
+        if constexpr (BOP == RED_LAYERNORM) y += PRE ? bv[PRE ? j : 0] : Elem<T>::load(p.beta, k);
         Elem<T>::store(p.y, oo + (int32_t)k * p.ors, y);
       }
     }
@@ -574,6 +587,19 @@ __global__ __launch_bounds__(1024) void red_colb_kernel(RedParams p) {
     if constexpr (SUM) a += ld1(rx1, vo1, (kb + (uint32_t)(KQ * j)) * xstep1);
     return a;
   };
+  // gamma and beta at min(k, R - 1), in bounds for k past the row: fetched with
+  // the row, not after the reduction, where they fit the registers, so that a
+  // launch of few workgroups costs one memory round trip
+  constexpr bool PRE = OP != RED_SOFTMAX && KPL <= 8;
+  float gv[PRE ? KPL : 1], bv[PRE && BOP == RED_LAYERNORM ? KPL : 1];
+  if constexpr (PRE) {
+#pragma unroll
+    for (int j = 0; j < KPL; ++j) {
+      const uint32_t kc = min(kl + KQ * j, R - 1u);
+      gv[j] = Elem<T>::load(p.gamma, kc);
+      if constexpr (BOP == RED_LAYERNORM) bv[j] = Elem<T>::load(p.beta, kc);
+    }
+  }
   auto st1 = [&](int j, uint32_t vo, float y) {
     const uint32_t so = (kb + (uint32_t)(KQ * j)) * ystep;
     if constexpr (ES == 4) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, y), ry, vo, so, 0);
@@ -665,11 +691,10 @@ __global__ __launch_bounds__(1024) void red_colb_kernel(RedParams p) {
     } else {
       rstd = 1.0f / sqrtf(sum * invR + p.attr);
     }
-    // gamma and beta are read at min(k, R - 1): in bounds for k past the row
     store_all([&](int j) {
       const uint32_t kc = min(kl + KQ * j, R - 1u);
-      float y = (v[j] - mean) * rstd * Elem<T>::load(p.gamma, kc);
-      if constexpr (BOP == RED_LAYERNORM) y += Elem<T>::load(p.beta, kc);
+      float y = (v[j] - mean) * rstd * (PRE ? gv[PRE ? j : 0] : Elem<T>::load(p.gamma, kc));
+      if constexpr (BOP == RED_LAYERNORM) y += PRE ? bv[PRE ? j : 0] : Elem<T>::load(p.beta, kc);
       return y;
     });
   }
@@ -681,11 +706,28 @@ template <typename T, int OP>
 hipError_t red_dispatch_op(const NodeKernel& k, hipStream_t s) {
   const RedParams& p = k.red;
   if (k.family == KF_RED_COL) {
-    // register-resident variant: byte offsets below 2^31, at most 32 values
-    // per lane; 64-row tiles where they still give 512 workgroups, else 16-
-    // or (for rows longer than 2048) 8-row tiles
+    // Register-resident variant: byte offsets below 2^31, at most 32 values
+    // per lane.  Rows RT of a tile, us per launch measured back to back:
+    //  * a tile of RT rows keeps nrows / RT workgroups busy, and an operand
+    //    whose unit-stride dim is the reduced one is read in runs of 64 / RT
+    //    values.  Few rows, or (`mixed`) such an operand beside another, want
+    //    a small RT: the sum-LayerNorm of 128 x 768 from column-major into
+    //    row-major 16.6 us with RT 16, 6.8 with 8, 4.5 with 4; of 16 x 1024
+    //    18.7, 7.2, 4.4; of 16384 x 1024 79, 48, 49.  Rows longer than 4096
+    //    fit the registers with RT 4 only.
+    //  * with every operand column-major and many rows, runs of RT
+    //    neighbouring rows are what is read: softmax of 6144 x 512 12.7 us
+    //    with RT 4, 9.0 with 8, 7.4 with 16 (but 1024 x 1024 5.8, 5.4, 6.7);
+    //    64-row tiles where they still give 512 workgroups.
+    //  * of rows no longer than 256 RT 4 leaves wavefronts without work, and
+    //    so does RT 8 of rows no longer than 64: 1536 x 128 4.4, 3.5, 4.1.
     const bool fits = (uint64_t)p.nrows * p.R * sizeof(T) < (uint64_t(1) << 31);
-    const int rt = ((p.nrows + 63u) / 64u >= 512u && p.R <= 512u) ? 64 : p.R <= 2048u ? 16 : 8;
+    const bool mixed = p.irs == 1 || p.ors == 1 || (red_has_sum(OP) && p.irs1 == 1);
+    int rt = 8;
+    if (p.R > 4096u || (p.nrows <= 1024u && p.R > 256u)) rt = 4;
+    else if (p.R <= 64u) rt = 16;
+    else if (!mixed && p.nrows > 2048u && p.R <= 2048u) rt = 16;
+    if (!mixed && (p.nrows + 63u) / 64u >= 512u && p.R <= 512u) rt = 64;
     const uint32_t kpl = (p.R + 16u * (64 / rt) - 1u) / (16u * (64 / rt));
 #define FLUID_COLB(RTv, K) \
   hipLaunchKernelGGL((red_colb_kernel<T, RTv, K, OP>), dim3((p.nrows + RTv - 1u) / RTv), dim3(1024), 0, s, p)
@@ -702,6 +744,8 @@ hipError_t red_dispatch_op(const NodeKernel& k, hipStream_t s) {
       FLUID_COLB_RT(64)
     } else if (rt == 16) {
       FLUID_COLB_RT(16)
+    } else if (rt == 4) {
+      FLUID_COLB_RT(4)
     } else {
       FLUID_COLB_RT(8)
     }
