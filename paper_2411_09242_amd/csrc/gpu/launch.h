@@ -14,6 +14,7 @@ hipError_t launch_gemm(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemm_bf16_pipe(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemm_bf16_dl(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemm_bf16_qk(const NodeKernel& k, hipStream_t s);
+hipError_t launch_gemm_bf16_skd(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemm_f32_dl(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemm_f32_split(const NodeKernel& k, hipStream_t s);
 // One launch for the G.n products of G, all of k's tile, operand modes and
