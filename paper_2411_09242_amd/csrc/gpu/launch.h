@@ -16,6 +16,7 @@ hipError_t launch_gemm_bf16_dl(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemm_bf16_qk(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemm_bf16_skd(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemm_f32_dl(const NodeKernel& k, hipStream_t s);
+hipError_t launch_gemv_f32(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemm_f32_split(const NodeKernel& k, hipStream_t s);
 // One launch for the G.n products of G, all of k's tile, operand modes and
 // epilogue instance (fp32 tiles 6 and 7).
