@@ -45,10 +45,10 @@ __device__ __forceinline__ void store_vec(void* p, int32_t off, const float* v) 
     *(float4*)((float*)p + off) = make_float4(v[0], v[1], v[2], v[3]);
   } else {
     uint4 q;
-    q.x = (uint32_t)f32_to_bf16(v[0]) | ((uint32_t)f32_to_bf16(v[1]) << 16);
-    q.y = (uint32_t)f32_to_bf16(v[2]) | ((uint32_t)f32_to_bf16(v[3]) << 16);
-    q.z = (uint32_t)f32_to_bf16(v[4]) | ((uint32_t)f32_to_bf16(v[5]) << 16);
-    q.w = (uint32_t)f32_to_bf16(v[6]) | ((uint32_t)f32_to_bf16(v[7]) << 16);
+    q.x = pack_bf16(v[0], v[1]);
+    q.y = pack_bf16(v[2], v[3]);
+    q.z = pack_bf16(v[4], v[5]);
+    q.w = pack_bf16(v[6], v[7]);
     *(uint4*)((uint16_t*)p + off) = q;
   }
 }

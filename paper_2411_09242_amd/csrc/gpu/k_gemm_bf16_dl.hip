@@ -284,8 +284,8 @@ void gemm_bf16_dl_kernel(GemmParams p) {
 #pragma unroll
           for (int vg = 0; vg < 4; ++vg) {
             const int r0 = i * 32 + 8 * vg + 4 * lh, c = j * 32 + lr;
-            const uint32_t lo = (uint32_t)f32_to_bf16(acc[i][j][4 * vg]) | ((uint32_t)f32_to_bf16(acc[i][j][4 * vg + 1]) << 16);
-            const uint32_t hi = (uint32_t)f32_to_bf16(acc[i][j][4 * vg + 2]) | ((uint32_t)f32_to_bf16(acc[i][j][4 * vg + 3]) << 16);
+            const uint32_t lo = pack_bf16(acc[i][j][4 * vg], acc[i][j][4 * vg + 1]);
+            const uint32_t hi = pack_bf16(acc[i][j][4 * vg + 2], acc[i][j][4 * vg + 3]);
             *(uint2*)&half(c >> 6)[(c & 63) * 64 + ((((r0 >> 3) ^ ((c >> 1) & 7))) << 3) + (r0 & 7)] = make_uint2(lo, hi);
           }
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)

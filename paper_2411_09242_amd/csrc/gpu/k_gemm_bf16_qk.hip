@@ -249,8 +249,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
             for (int vg = 0; vg < 4; ++vg) {
               const int r0 = wm * 64 + 32 * i + 8 * vg + 4 * lh, c = wn * 64 + 32 * j + lr;
-              const uint32_t lo = (uint32_t)f32_to_bf16(acc[i][j][4 * vg]) | ((uint32_t)f32_to_bf16(acc[i][j][4 * vg + 1]) << 16);
-              const uint32_t hi = (uint32_t)f32_to_bf16(acc[i][j][4 * vg + 2]) | ((uint32_t)f32_to_bf16(acc[i][j][4 * vg + 3]) << 16);
+              const uint32_t lo = pack_bf16(acc[i][j][4 * vg], acc[i][j][4 * vg + 1]);
+              const uint32_t hi = pack_bf16(acc[i][j][4 * vg + 2], acc[i][j][4 * vg + 3]);
               *(uint2*)&cs[c * QK_T + (((r0 >> 3) ^ (c & 15)) << 3) + (r0 & 7)] = make_uint2(lo, hi);
             }
         lds_barrier();

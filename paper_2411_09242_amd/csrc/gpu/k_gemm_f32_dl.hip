@@ -47,7 +47,6 @@ namespace {
 constexpr int SK_TN = 32;            // output tile columns
 constexpr int SK_FN = 2;             // 16 x 16 blocks across a tile
 typedef __attribute__((address_space(3))) void lds_void;
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 
 }  // namespace
 
