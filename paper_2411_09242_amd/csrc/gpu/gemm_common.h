@@ -39,7 +39,7 @@ __device__ __forceinline__ uint16_t bload2(Rsrc r, uint32_t off) {
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
 
 // Tile index -> (batch, tile row, tile column), row-major over tiles.
-__device__ __forceinline__ TileCoord tile_coord_at(const GemmParams& p, uint32_t bid, uint32_t BM, uint32_t BN) {
+__device__ __forceinline__ TileCoord tile_coord_lin(const GemmParams& p, uint32_t bid, uint32_t BM, uint32_t BN) {
   const uint32_t per_g = p.tiles_m * p.tiles_n;
   const uint32_t g = bid / per_g;
   const uint32_t r = bid - g * per_g;
@@ -55,6 +55,24 @@ __device__ __forceinline__ TileCoord tile_coord_at(const GemmParams& p, uint32_t
   t.c_base = (int32_t)g1 * p.c_g1 + (int32_t)g2 * p.c_g2;
   t.r_base = (int32_t)g1 * p.r_g1 + (int32_t)g2 * p.r_g2;
   return t;
+}
+// The tile of workgroup bid.  Where the K loop stops at a tile's last row
+// (causal bit 1) the work of tile row tm is proportional to tm + 1, and in
+// row-major order workgroup bid, which runs on XCD bid % 8, has tile row
+// bid % 8 of its head when a head has eight: one XCD gets every long tile.
+// So: tile rows from the longest to the shortest, the heads fastest (a head
+// stays on one XCD), and every second run of 256 workgroups, one for every
+// CU, backwards, so that a CU with two of them gets a long and a short tile.
+// P V of 32 heads of 2048 x 2048, D 128, bf16 (256 tiles): 96 -> 85 us.
+__device__ __forceinline__ TileCoord tile_coord_at(const GemmParams& p, uint32_t bid, uint32_t BM, uint32_t BN) {
+  if (p.causal & 2u) {
+    const uint32_t per_m = p.tiles_n * p.G, total = p.tiles_m * per_m;
+    uint32_t i = bid;
+    if ((i & 256u) && (i | 255u) < total) i ^= 248u;  // eight by eight: bid % 8 stays
+    const uint32_t m = i / per_m, q = i - m * per_m, tn = q / p.G, g = q - tn * p.G;
+    bid = (g * p.tiles_m + (p.tiles_m - 1u - m)) * p.tiles_n + tn;
+  }
+  return tile_coord_lin(p, bid, BM, BN);
 }
 // One workgroup per tile.
 __device__ __forceinline__ TileCoord tile_coord(const GemmParams& p, uint32_t BM, uint32_t BN) {

@@ -36,7 +36,7 @@ __device__ __forceinline__ TileCoord split_tile(const GemmParams& p, uint32_t BM
   const uint32_t band = r / (4 * p.tiles_n), first = 4 * band;
   const uint32_t rows = min(4u, p.tiles_m - first);
   const uint32_t q = r - band * 4 * p.tiles_n;
-  return tile_coord_at(p, g * per_g + (first + q % rows) * p.tiles_n + q / rows, BM, BN);
+  return tile_coord_lin(p, g * per_g + (first + q % rows) * p.tiles_n + q / rows, BM, BN);
 }
 
 }  // namespace
