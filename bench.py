@@ -56,7 +56,8 @@ TRAFFIC = {
 }
 
 # the device sources of each kernel family (by launch-name prefix)
-FAMILY_SOURCES = {"gemm": ["k_gemm*.hip", "gemm_common.h", "dev.h"], "conv": ["k_conv.hip", "dev.h"],
+FAMILY_SOURCES = {"gemm": ["k_gemm*.hip", "gemm_common.h", "split_common.h", "dev.h"],
+                  "conv": ["k_conv*.hip", "gemm_common.h", "split_common.h", "dev.h"],
                   "": ["k_elementwise.hip", "k_reduce.hip", "dev.h"]}
 
 
