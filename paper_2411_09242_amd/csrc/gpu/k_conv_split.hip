@@ -213,7 +213,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int j = 0; j < FJ; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] += low[i][j][v];
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = (acc[i][j][v] + low[i][j][v]) * kSplitUnscale;
 
   // The groups' partial sums, in pieces of four rows of a 32 x 32 block:
   // group g finishes pieces g OWN .. +OWN-1 and parks the others.

@@ -2,20 +2,24 @@
 // or K-contiguous B.  Every fp32 value x is written exactly as the sum of
 // three bf16 values (24 = 3 x 8 significant bits):
 //   h = bf16(x),  m = bf16(x - h),  l = bf16(x - h - m)
-// (both differences are exact), and a product a b is summed from the six
-// partial products h h', h m', m h', m m', h l', l h', each exact in the
-// fp32 accumulator's input; the dropped m l', l m', l l' are below 2^-25 of
-// |a b|, half the rounding of one fp32 multiply-add.  The bf16 cores run 16
-// times the fp32 ones' rate, so six products still leave 2.7 times the fp32
-// matrix peak, and an accumulator is rounded once per 16 k of a product
-// (6 / 16 per k) instead of every 2 k by the fp32 MFMA.
+// (both differences are exact; the decomposition of Henry, Tang and Heinecke,
+// "Leveraging the bfloat16 Artificial Intelligence Datatype For
+// Higher-Precision Computations", ARITH 2019), and a product a b is summed
+// from the six partial products h h', h m', m h', m m', h l', l h', each
+// exact in the fp32 accumulator's input; of the dropped ones m l' and l m'
+// are at most 2^-25 of |a b| each, together the rounding of one fp32
+// multiply-add.  The bf16 cores run 16 times the fp32 ones' rate, so six
+// products still leave 2.7 times the fp32 matrix peak, and an accumulator is
+// rounded once per 16 k of a product (6 / 16 per k) instead of every 2 k by
+// the fp32 MFMA.  The operands are scaled (split_common.h), so that this
+// holds for every finite operand, subnormal ones too.
 //
-// Exceptions of the split, all found after the product: an infinity (its
-// x - h is NaN), a finite value that rounds to a bf16 infinity, and an
-// overflowing sum leave a non-finite accumulator.  A workgroup that sees
-// one recomputes its tile with the fp32 MFMA straight from memory, so that
-// infinities, NaN and values up to the largest float behave as in fp32.
-// (An l below 2^-126 loses bits: relevant for |x| below 2^-108.)
+// Exceptions of the split, all found after the product: an infinity or NaN
+// (its x - h is NaN), a value of 2^104 or more (its scaled h is an infinity)
+// and a sum that reaches 2^80 leave a non-finite accumulator.  A workgroup
+// that sees one recomputes its tile with the fp32 MFMA straight from memory,
+// so that infinities, NaN and values up to the largest float behave as in
+// fp32.
 #include "launch.h"
 #include "split_common.h"
 
@@ -243,7 +247,7 @@ void gemm_f32_split_kernel(GemmParams p) {
 #pragma unroll
     for (int j = 0; j < FJ; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] += low[i][j][v];
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = (acc[i][j][v] + low[i][j][v]) * kSplitUnscale;
 
   // the groups' partial sums: every wavefront parks the blocks that other
   // groups finish and adds theirs to its own, in group order

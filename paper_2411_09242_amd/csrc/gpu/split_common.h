@@ -6,8 +6,16 @@
 
 namespace fluid {
 
-// The three bf16 parts of the pair (a, b): plane 0 the leading parts.
+// Both operands are multiplied by 2^24 before they are split, and the sums
+// by 2^-48: the lowest bit of any fp32 value, 2^-149, becomes 2^-125, so that
+// every part of every value is a normal bf16 number (without the scale an
+// operand of 1e-36 keeps 16 bits, one of 1e-40 two).
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;
+
+// The three bf16 parts of the scaled pair (a, b): plane 0 the leading parts.
 __device__ __forceinline__ void split2(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+  a *= kSplitScale;
+  b *= kSplitScale;
   h = pack_bf16(a, b);
   a -= __uint_as_float(h << 16);
   b -= __uint_as_float(h & 0xffff0000u);

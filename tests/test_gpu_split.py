@@ -166,3 +166,43 @@ def test_split_convolution(case, variant):
     got = convolution(variant, x, w, b)
     assert (np.isnan(got) == np.isnan(ref)).all() and (got[np.isinf(ref)] == ref[np.isinf(ref)]).all()
     assert np.isfinite(got[np.isfinite(ref)]).all()
+
+
+# operand sizes whose bf16 parts, unscaled, would be subnormal or vanish, each
+# beside a size that makes the products ordinary floats; the last pair's sums
+# leave the range of the scaled accumulator
+SIZES = [(1e-31, 1e31), (1e-36, 1e36), (1e-38, 1e37), (1e-40, 1e37), (1e-44, 1e37), (1e36, 1e-36), (1e15, 1e15)]
+
+
+@pytest.mark.parametrize("sizes", SIZES, ids=str)
+@pytest.mark.parametrize("variant", VARIANTS)
+def test_split_operand_sizes(sizes, variant):
+    """Small, subnormal and large operands: the bound of any fp32 summation
+    (plus half the smallest float per product)."""
+    rng = np.random.default_rng(9)
+    M, K, N = 132, 68, 136
+    x = (sizes[0] * rng.standard_normal((M, K))).astype(np.float32)
+    w = (sizes[1] * rng.standard_normal((K, N))).astype(np.float32)
+    x[rng.random((M, K)) < 0.1] = 0.0
+    exact = x.astype(np.float64) @ w.astype(np.float64)
+    bound = (K + 1) * (2.0 ** -24 * (np.abs(x).astype(np.float64) @ np.abs(w)) + 2.0 ** -150)
+    say("sizes", sizes, variant)
+    assert (np.abs(product(variant, x, w) - exact) <= bound).all()
+
+
+@pytest.mark.parametrize("sizes", SIZES, ids=str)
+@pytest.mark.parametrize("variant", [0, 2, 4])
+def test_split_convolution_operand_sizes(sizes, variant):
+    from numpy.lib.stride_tricks import sliding_window_view
+    rng = np.random.default_rng(10)
+    x = (sizes[0] * rng.standard_normal((1, 6, 9, 11))).astype(np.float32)
+    w = (sizes[1] * rng.standard_normal((33, 6, 3, 3))).astype(np.float32)
+
+    def exact(x, w):
+        win = sliding_window_view(x.astype(np.float64), (3, 3), axis=(2, 3))
+        return np.einsum("nchwuv,ocuv->nohw", win, w.astype(np.float64))
+
+    bound = (6 * 9 + 1) * (2.0 ** -24 * exact(np.abs(x), np.abs(w)) + 2.0 ** -150)
+    say("conv sizes", sizes, variant)
+    got = convolution(variant, x, w, np.zeros(33, np.float32))
+    assert (np.abs(got - exact(x, w)) <= bound).all()
