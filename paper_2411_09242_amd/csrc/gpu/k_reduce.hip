@@ -744,18 +744,23 @@ hipError_t red_dispatch_op(const NodeKernel& k, hipStream_t s) {
     //    row-major 16.6 us with RT 16, 6.8 with 8, 4.5 with 4; of 16 x 1024
     //    18.7, 7.2, 4.4; of 16384 x 1024 79, 48, 49.  Rows longer than 4096
     //    fit the registers with RT 4 only.
-    //  * with every operand column-major and many rows, runs of RT
-    //    neighbouring rows are what is read: softmax of 6144 x 512 12.7 us
-    //    with RT 4, 9.0 with 8, 7.4 with 16 (but 1024 x 1024 5.8, 5.4, 6.7);
-    //    64-row tiles where they still give 512 workgroups.
+    //  * with every operand column-major, runs of RT neighbouring rows are
+    //    what is read, in whole lines only where a run is long enough: the
+    //    LayerNorm of 512 x 1024 6.2 us with RT 4, 6.3 with 8, 8.2 with 16; of
+    //    700 x 1024 9.4, 7.6, 8.8; of 1024 x 2048 10.4, 9.8, 12.7; of 8192 x
+    //    512 17.6, 11.6, 9.8 (with 64 14.6); 64-row tiles where they still
+    //    give 512 workgroups.
     //  * of rows no longer than 256 RT 4 leaves wavefronts without work, and
-    //    so does RT 8 of rows no longer than 64: 1536 x 128 4.4, 3.5, 4.1.
+    //    so does RT 8 of rows no longer than 64, or, with many rows, 128: 8192
+    //    x 96, mixed, 13.1, 8.4, 7.2.
     const bool fits = (uint64_t)p.nrows * p.R * sizeof(T) < (uint64_t(1) << 31);
     const bool mixed = p.irs == 1 || p.ors == 1 || (red_has_sum(OP) && p.irs1 == 1);
     int rt = 8;
-    if (p.R > 4096u || (p.nrows <= 1024u && p.R > 256u)) rt = 4;
+    if (p.R > 4096u) rt = 4;
     else if (p.R <= 64u) rt = 16;
-    else if (!mixed && p.nrows > 2048u && p.R <= 2048u) rt = 16;
+    else if (mixed) rt = p.nrows <= 1024u && p.R >= 256u ? 4 : p.nrows > 2048u && p.R <= 128u ? 16 : 8;
+    else if (p.nrows <= 512u) rt = p.R > 256u ? 4 : 8;
+    else if (p.nrows > 2048u && p.R <= 2048u) rt = 16;
     if (!mixed && (p.nrows + 63u) / 64u >= 512u && p.R <= 512u) rt = 64;
     const uint32_t kpl = (p.R + 16u * (64 / rt) - 1u) / (16u * (64 / rt));
 #define FLUID_COLB(RTv, K) \

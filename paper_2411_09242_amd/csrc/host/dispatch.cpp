@@ -273,7 +273,12 @@ NodeKernel prepare_red(const Node& nd, int variant, int dtype, const std::vector
     bool q = p.causal && i == r - 2;
     if (x.shape[i] != 1 || q) rows.push_back({x.shape[i], x.stride[i], out.stride[i], x1 ? x1->stride[i] : 0, q});
   }
-  std::stable_sort(rows.begin(), rows.end(), [](const D& a, const D& b) { return a.is > b.is; });
+  // Row order: by input stride; for the column variant, whose tiles are runs
+  // of neighbouring rows, by the strides of the first operand that is not
+  // read or written along the row anyway (x, x1, the output).
+  int64_t D::*key = &D::is;
+  if (variant == 1 && p.irs == 1) key = x1 && p.irs1 != 1 ? &D::is1 : p.ors != 1 ? &D::os : &D::is;
+  std::stable_sort(rows.begin(), rows.end(), [key](const D& a, const D& b) { return a.*key > b.*key; });
   if (rows.size() > (size_t)kMaxDims) fail(FLUID_E_UNSUPPORTED, "reduction rank");
   p.nrd = (int)rows.size();
   p.qdim = -1;
