@@ -732,10 +732,7 @@ hipError_t launch_gemm(const NodeKernel& k, hipStream_t s) {
   const GemmParams& p = k.gemm;
   if ((uint64_t)p.tiles_m * p.tiles_n * p.G >= (1ull << 31)) return hipErrorInvalidValue;
   if (k.gemm_tile >= 8 && k.dtype == DT_F32) return launch_gemm_f32_split(k, s);
-  // tile 6, at most four rows, K-contiguous operands: the row-times-matrix
-  // kernel
-  if (k.gemm_tile == 6 && k.dtype == DT_F32 && p.M <= 4 && p.G == 1 && k.amode == GM_K && k.bmode == GM_K && !p.causal)
-    return launch_gemv_f32(k, s);
+  if (k.gemm_row) return launch_gemv_f32(k, s);
   if (k.gemm_tile >= 6) return k.dtype == DT_BF16 ? launch_gemm_bf16_pipe(k, s) : launch_gemm_f32_dl(k, s);
   // bf16, both operands K-contiguous and below 2 GiB (buffer loads): the DMA
   // kernel, faster at every size measured from 16 x 1024 x 1024 on (4.8

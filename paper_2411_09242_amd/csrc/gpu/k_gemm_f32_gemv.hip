@@ -6,7 +6,7 @@
 // wavefronts takes four columns: its threads read 4 KiB runs of each
 // column's K values, sixteen bytes a lane, with the rows of A from the
 // caches, and the lanes' sums are added across the wavefront and through LDS
-// in wavefront order.  Everything is fp32; a lane's chain is K / 1024 long.
+// in wavefront order.  Everything is fp32; a lane's chain is K / 256 long.
 // The three dense layers of the VGG-16-shaped network (25088, 4096, 4096 x
 // 4096, 4096, 1000) with it: 975 -> 906 us for the network, where they took
 // 114, 22 and 20 us (3.6, 3.0 and 0.8 TB/s).
@@ -17,12 +17,13 @@
 
 namespace fluid {
 
+// Columns 4 bid .. 4 bid + 3 of the product p.
 template <int MR, bool RES>
-__global__ __launch_bounds__(256) void gemv_f32_kernel(GemmParams p) {
+__device__ __forceinline__ void gemv_f32_cols(const GemmParams& p, uint32_t bid) {
   constexpr int NC = 4, U = MR == 1 ? 4 : 2;
   __shared__ float part[4][NC * MR];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint32_t n0 = blockIdx.x * NC;
+  const uint32_t n0 = bid * NC;
   const float* A = (const float*)p.A;
   const float* B = (const float*)p.B;
   // rows past M and columns past N are clamped onto the first: never stored
@@ -80,10 +81,24 @@ __global__ __launch_bounds__(256) void gemv_f32_kernel(GemmParams p) {
   }
 }
 
+template <int MR, bool RES>
+__global__ __launch_bounds__(256) void gemv_f32_kernel(GemmParams p) {
+  gemv_f32_cols<MR, RES>(p, blockIdx.x);
+}
+
+// The members of a group share the rows and the epilogue instance; each
+// workgroup runs four columns of its member.
+template <int MR, bool RES>
+__global__ __launch_bounds__(256) void gemv_f32_group_kernel(GemmGroup G) {
+  uint32_t i = 0;
+  while (i + 1 < G.n && blockIdx.x >= G.tiles[i + 1]) ++i;
+  gemv_f32_cols<MR, RES>(G.p[i], blockIdx.x - G.tiles[i]);
+}
+
 hipError_t launch_gemv_f32(const NodeKernel& k, hipStream_t s) {
   const GemmParams& p = k.gemm;
   if (p.M > 4 || p.G != 1) return hipErrorInvalidValue;
-  const dim3 grid((p.N + 3) / 4);
+  const dim3 grid(p.tiles_n);
 #define FLUID_GEMV(MRv)                                                                        \
   do {                                                                                         \
     if (p.rop) hipLaunchKernelGGL((gemv_f32_kernel<MRv, true>), grid, dim3(256), 0, s, p);     \
@@ -93,6 +108,23 @@ hipError_t launch_gemv_f32(const NodeKernel& k, hipStream_t s) {
   else if (p.M == 2) FLUID_GEMV(2);
   else FLUID_GEMV(4);
 #undef FLUID_GEMV
+  return hipGetLastError();
+}
+
+hipError_t launch_gemv_f32_group(const NodeKernel& k, const GemmGroup& G, hipStream_t s) {
+  if (!k.gemm_row || G.n < 1 || G.n > (uint32_t)kMaxGroup) return hipErrorInvalidValue;
+  for (uint32_t i = 0; i < G.n; ++i)
+    if (G.p[i].M != k.gemm.M || G.p[i].G != 1) return hipErrorInvalidValue;
+  const dim3 grid(G.tiles[G.n]);
+#define FLUID_GEMVG(MRv)                                                                              \
+  do {                                                                                                \
+    if (k.gemm.rop) hipLaunchKernelGGL((gemv_f32_group_kernel<MRv, true>), grid, dim3(256), 0, s, G); \
+    else hipLaunchKernelGGL((gemv_f32_group_kernel<MRv, false>), grid, dim3(256), 0, s, G);           \
+  } while (0)
+  if (k.gemm.M == 1) FLUID_GEMVG(1);
+  else if (k.gemm.M == 2) FLUID_GEMVG(2);
+  else FLUID_GEMVG(4);
+#undef FLUID_GEMVG
   return hipGetLastError();
 }
 

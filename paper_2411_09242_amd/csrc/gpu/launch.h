@@ -18,9 +18,10 @@ hipError_t launch_gemm_bf16_skd(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemm_f32_dl(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemv_f32(const NodeKernel& k, hipStream_t s);
 hipError_t launch_gemm_f32_split(const NodeKernel& k, hipStream_t s);
-// One launch for the G.n products of G, all of k's tile, operand modes and
-// epilogue instance (fp32 tiles 6 and 7).
+// One launch for the G.n products of G, all of k's kernel (fp32 tiles 6 and
+// 7, or the row kernel), operand modes and epilogue instance.
 hipError_t launch_gemm_f32_dl_group(const NodeKernel& k, const GemmGroup& G, hipStream_t s);
+hipError_t launch_gemv_f32_group(const NodeKernel& k, const GemmGroup& G, hipStream_t s);
 hipError_t launch_fill(void* p, uint64_t bytes, uint32_t seed, hipStream_t s);
 hipError_t launch_window(const NodeKernel& k, hipStream_t s);
 hipError_t launch_conv(const NodeKernel& k, hipStream_t s);

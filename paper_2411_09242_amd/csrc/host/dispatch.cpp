@@ -320,6 +320,14 @@ NodeKernel prepare_red(const Node& nd, int variant, int dtype, const std::vector
   return k;
 }
 
+// Whether a product of fp32 tile 6 runs on the row-times-matrix kernel
+// (k_gemm_f32_gemv.hip): at most four rows, one batch, both operands
+// K-contiguous.
+bool row_product(const NodeKernel& k) {
+  const GemmParams& p = k.gemm;
+  return p.M <= 4 && p.G == 1 && k.amode == GM_K && k.bmode == GM_K && !p.causal;
+}
+
 NodeKernel prepare_gemm(const Node& nd, int variant, int dtype, const std::vector<Operand>& ins, const Operand& out) {
   NodeKernel k;
   if (packs_weight(nd.op, variant) && (nd.ins.size() != 2 || nd.ins[1] >= 0 || ins[1].shape.size() != 2)) {
@@ -464,6 +472,11 @@ NodeKernel prepare_gemm(const Node& nd, int variant, int dtype, const std::vecto
     k.available = false;
     k.why = "buffer-load tiles address at most 2 GiB per operand";
     return k;
+  }
+  if (tile == 6 && f32 && row_product(k)) {
+    k.gemm_row = true;
+    tm = 4;
+    tn = 4;
   }
   p.tiles_m = (p.M + tm - 1) / tm;
   p.tiles_n = (p.N + tn - 1) / tn;
@@ -643,7 +656,7 @@ std::string NodeKernel::name() const {
       };
       static const char* tiles[] = {"t128", "t64", "sk32w4", "sk32w8", "sk64x32w4", "sk32w16", "p256x128", "p128", "p256x128s3", "q128"};
       static const char* tiles_f32[] = {"t128", "t64", "sk32w4", "sk32w8", "sk64x32w4", "sk32w16", "dl16x32w8", "dl32w4", "s256x128", "s128"};
-      return "gemm_" + dt + "_" + (dtype == DT_BF16 ? tiles : tiles_f32)[gemm_tile] + "_a" + gm[amode] + "_b" + gm[bmode] + "_c" +
+      return "gemm_" + dt + "_" + (gemm_row ? "row4" : (dtype == DT_BF16 ? tiles : tiles_f32)[gemm_tile]) + "_a" + gm[amode] + "_b" + gm[bmode] + "_c" +
              (cmode == 1 ? "n" : cmode == 2 ? "m" : "g") + (gemm.causal ? "_causal" + std::to_string(gemm.causal) : "") +
              epi_suffix();
     }

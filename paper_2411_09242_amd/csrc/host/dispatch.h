@@ -57,6 +57,7 @@ struct NodeKernel {
   int conv_kord = 0, conv_ks = 1, conv_tile = 64, conv_bm = 0;
   bool red_block = false;       // row reduction: one 256-thread workgroup per row (variant 2)
   int gemm_tile = 0, amode = 0, bmode = 0, cmode = 0;  // cmode 0 generic, 1 N-contig, 2 M-contig
+  bool gemm_row = false;        // fp32 tile 6 on at most four rows: the row-times-matrix kernel
   std::string name() const;
 };
 

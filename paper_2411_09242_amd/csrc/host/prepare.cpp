@@ -199,7 +199,8 @@ std::vector<std::pair<int, Bind>> read_operands(const Graph& g, const Prepared& 
 }
 
 // Grouped launches.  Consecutive launches of fp32 products with the same
-// direct-load tile (6 or 7), operand modes and epilogue instance -- the Q,
+// direct-load tile (6 or 7) or row kernel (and then rows), operand modes and
+// epilogue instance -- the Q,
 // K and V projections of a layer once their bias Adds are fused and their
 // head reshapes are views -- go out as one launch when none reads or
 // overwrites what another writes (they run concurrently).
@@ -220,7 +221,8 @@ void group_launches(const Graph& g, const ArenaPlan* ap, Prepared& P) {
     std::vector<size_t> mem = {i};
     for (size_t j = next_launch(i); j < P.nodes.size() && mem.size() < (size_t)kMaxGroup; j = next_launch(j)) {
       const NodeKernel &a = kern(i), &b = kern(j);
-      if (!eligible(j) || b.gemm_tile != a.gemm_tile || b.amode != a.amode || b.bmode != a.bmode ||
+      if (!eligible(j) || b.gemm_tile != a.gemm_tile || b.gemm_row != a.gemm_row ||
+          (a.gemm_row && b.gemm.M != a.gemm.M) || b.amode != a.amode || b.bmode != a.bmode ||
           (b.gemm.rop != 0) != (a.gemm.rop != 0))
         break;
       bool indep = true;

@@ -8,7 +8,7 @@ import pytest
 
 from gpu_util import assert_close, forced_table, random_inputs, run_device, say
 from oracle import execute
-from test_gpu_ops import EPILOGUES, _check_gemm, epilogue_graph, proj_graph
+from test_gpu_ops import EPILOGUES, _check_gemm, epilogue_graph, proj_graph, reference_rounding_except, siblings_graph
 
 pytestmark = pytest.mark.gpu
 
@@ -21,7 +21,7 @@ def test_few_rows(K, rows, N, tmp_path):
     og, a, c = proj_graph(B, S, K, N, "f32")
     say(f"few rows {rows} K {K} N {N}")
     lp = _check_gemm(og, {}, {1: 16}, tmp_path, K + N, "f32")
-    assert lp.kernel(1).startswith("gemm_f32_dl16x32w8_ak_bk_")
+    assert lp.kernel(1).startswith("gemm_f32_row4_ak_bk_")
 
 
 @pytest.mark.parametrize("rows", [(1, 1), (1, 3)], ids=str)
@@ -35,3 +35,42 @@ def test_few_rows_epilogue(rows, chain, tmp_path):
     say(f"few rows {rows} {chain}")
     out, lp, _ = run_device(og, forced_table(og, {}, {mm: 16}), xs, cs, tmp_path, no_reuse=True)
     assert_close(out[0], ref, "f32", f"{rows} {chain}")
+
+
+@pytest.mark.parametrize("rows", [(1, 1), (1, 2), (3, 1), (2, 2)], ids=str)
+@pytest.mark.parametrize("K", [68, 4100])
+def test_few_rows_grouped(rows, K, tmp_path):
+    """Q, K and V products of at most four rows, each with its bias, in one
+    launch of the row kernel: the oracle's result, and bit for bit what the
+    same products give when they are launched one by one."""
+    import json
+
+    import torch
+    from paper_2411_09242_amd import fluid as F
+    og, prods, outs = siblings_graph(*rows, K, 43, "f32")
+    mms = [i for i, nd in enumerate(og.nodes) if nd.op == "matmul"]
+    xs, cs = random_inputs(og, K)
+    path = tmp_path / "table.json"
+    path.write_text(json.dumps(forced_table(og, {}, {m: 16 for m in mms})))
+    g = F.Graph.from_desc(og.export())
+    lp = F.LayoutPlan(g, F.CostTable.load(str(path), g))
+    ap = F.ArenaPlan(g, lp, no_reuse=True, epilogue=True)
+    ex = F.Executor(g, lp, ap, cs, xs)
+    launch, _, names = ex.schedule()
+    assert len({launch[m] for m in mms}) == 1
+    assert names[launch[mms[0]]].startswith("gemm_f32_row4_") and names[launch[mms[0]]].endswith("_eb_x3")
+    say(f"few rows grouped {rows} K {K}")
+    ex.arena.fill_(0xFF)
+    whole = ex.run()[0].clone()
+    ref = reference_rounding_except(og, xs, cs, set(prods))
+    torch.cuda.synchronize()
+    assert_close(whole.cpu().numpy(), ref[0], "f32", f"{rows} {K}")
+    ex.arena.fill_(0xFF)
+    ex.outputs[0].fill_(float("nan"))
+    for n in range(g.n_nodes):       # one call per node (a product with its bias Add)
+        if n in mms:
+            ex.run_nodes([n, n + 1])
+        elif n - 1 not in mms:
+            ex.run_nodes([n])
+    torch.cuda.synchronize()
+    assert torch.equal(ex.outputs[0], whole)
