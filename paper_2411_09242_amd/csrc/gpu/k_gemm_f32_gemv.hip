@@ -1,6 +1,7 @@
 // fp32 products of at most four rows with a K-contiguous weight (the fully
 // connected layers of a network run on one image): tile 6 for those
-// operands.  Such a product reads its weight once and is bound by that; the
+// operands where K is long enough (the rule and both sides' times: row_product
+// in dispatch.cpp).  Such a product reads its weight once and is bound by that; the
 // 16 x 32 tile kernel has N / 32 workgroups, too few loads in flight, and
 // multiplies twelve or more rows of padding.  Here a workgroup of four
 // wavefronts takes four columns: its threads read 4 KiB runs of each

@@ -322,10 +322,18 @@ NodeKernel prepare_red(const Node& nd, int variant, int dtype, const std::vector
 
 // Whether a product of fp32 tile 6 runs on the row-times-matrix kernel
 // (k_gemm_f32_gemv.hip): at most four rows, one batch, both operands
-// K-contiguous.
+// K-contiguous, and K long enough for its workgroups of four columns.  It
+// keeps 1, 2 or 4 rows and costs a launch of N / 4 workgroups, where the 16 x
+// 32 tile has N / 32 (us, row kernel and tile, K x N): one row 128 x 1000 4.1
+// and 4.4, 256 x 8192 6.2 and 5.7, 512 x 8192 6.5 and 6.8, 9216 x 4096 28.3
+// and 49.1; two rows 512 x 8192 9.0 and 6.9, 1024 x 4096 7.5 and 7.8, 4096 x
+// 1000 7.3 and 14.5; three or four 64 x 8192 14.2 and 4.4, 1024 x 4096 10.3
+// and 7.8, 2048 x 1000 8.3 and 9.9, 4096 x 4096 18.7 and 23.8.
 bool row_product(const NodeKernel& k) {
   const GemmParams& p = k.gemm;
-  return p.M <= 4 && p.G == 1 && k.amode == GM_K && k.bmode == GM_K && !p.causal;
+  if (p.M > 4 || p.G != 1 || k.amode != GM_K || k.bmode != GM_K || p.causal) return false;
+  const uint32_t kept = p.M <= 2 ? p.M : 4;
+  return p.K >= 512 * kept || (p.M == 1 && p.K >= 128 && p.N <= 4096);
 }
 
 NodeKernel prepare_gemm(const Node& nd, int variant, int dtype, const std::vector<Operand>& ins, const Operand& out) {

@@ -13,7 +13,12 @@ from test_gpu_ops import EPILOGUES, _check_gemm, epilogue_graph, proj_graph, ref
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("K", [4, 1020, 1028, 4096, 5124, 9000])
+def row_kernel(M, K, N):
+    """The rule by which variant 16 takes the row kernel."""
+    return K >= 512 * (M if M <= 2 else 4) or (M == 1 and K >= 128 and N <= 4096)
+
+
+@pytest.mark.parametrize("K", [4, 124, 128, 508, 512, 1020, 1028, 2044, 2048, 4096, 5124, 9000])
 @pytest.mark.parametrize("rows", [(1, 1), (1, 2), (3, 1), (2, 2), (1, 4)], ids=str)
 @pytest.mark.parametrize("N", [2, 5, 36])
 def test_few_rows(K, rows, N, tmp_path):
@@ -21,19 +26,21 @@ def test_few_rows(K, rows, N, tmp_path):
     og, a, c = proj_graph(B, S, K, N, "f32")
     say(f"few rows {rows} K {K} N {N}")
     lp = _check_gemm(og, {}, {1: 16}, tmp_path, K + N, "f32")
-    assert lp.kernel(1).startswith("gemm_f32_row4_ak_bk_")
+    tile = "row4" if row_kernel(B * S, K, N) else "dl16x32w8"
+    assert lp.kernel(1).startswith(f"gemm_f32_{tile}_ak_bk_")
 
 
 @pytest.mark.parametrize("rows", [(1, 1), (1, 3)], ids=str)
 @pytest.mark.parametrize("chain", sorted(EPILOGUES))
 def test_few_rows_epilogue(rows, chain, tmp_path):
     B, S = rows
-    og, a, r, edges = epilogue_graph(B, S, 68, 43, "f32", False, chain)
+    og, a, r, edges = epilogue_graph(B, S, 2052, 43, "f32", False, chain)
     mm = og.producer(edges[0])
     xs, cs = random_inputs(og, 5)
     (ref,) = execute.run_canonical(og, xs, cs)
     say(f"few rows {rows} {chain}")
     out, lp, _ = run_device(og, forced_table(og, {}, {mm: 16}), xs, cs, tmp_path, no_reuse=True)
+    assert lp.kernel(mm).startswith("gemm_f32_row4_ak_bk_")
     assert_close(out[0], ref, "f32", f"{rows} {chain}")
 
 
@@ -41,7 +48,7 @@ def test_few_rows_epilogue(rows, chain, tmp_path):
 @pytest.mark.parametrize("K", [68, 4100])
 def test_few_rows_grouped(rows, K, tmp_path):
     """Q, K and V products of at most four rows, each with its bias, in one
-    launch of the row kernel: the oracle's result, and bit for bit what the
+    launch (of the row kernel where K is long): the oracle's result, and bit for bit what the
     same products give when they are launched one by one."""
     import json
 
@@ -58,7 +65,8 @@ def test_few_rows_grouped(rows, K, tmp_path):
     ex = F.Executor(g, lp, ap, cs, xs)
     launch, _, names = ex.schedule()
     assert len({launch[m] for m in mms}) == 1
-    assert names[launch[mms[0]]].startswith("gemm_f32_row4_") and names[launch[mms[0]]].endswith("_eb_x3")
+    tile = "row4" if row_kernel(rows[0] * rows[1], K, 43) else "dl16x32w8"
+    assert names[launch[mms[0]]].startswith(f"gemm_f32_{tile}_") and names[launch[mms[0]]].endswith("_eb_x3")
     say(f"few rows grouped {rows} K {K}")
     ex.arena.fill_(0xFF)
     whole = ex.run()[0].clone()
