@@ -50,10 +50,12 @@ __device__ __forceinline__ TileCoord split_tile(const GemmParams& p, uint32_t BM
 // group order at the end).  A CU holds one workgroup of eight wavefronts, so
 // that every SIMD has two to issue from:
 //  * 256 x 128 (KS 1): 1.5 times the MFMAs per split element and per LDS
-//    write of the smaller tile; for outputs with a tile for every CU.
-//  * 128 x 128 (KS 2): for outputs with 256 tiles or fewer of it, where the
-//    larger tile would leave CUs idle; two groups over K rather than 64 x 32
-//    wavefront tiles, which would read LDS half as much again per MFMA.
+//    write of the smaller tile; K-contiguous A only (with an M-contiguous
+//    one it spills 15 to 22 VGPRs).
+//  * 128 x 128 (KS 2): where the larger tile would leave CUs idle; two groups
+//    over K rather than 64 x 32 wavefront tiles, which would read LDS half as
+//    much again per MFMA.
+//  Which of them runs: split_tile_of in dispatch.cpp.
 // Measured (weights from HBM), 128 x 128 / 256 x 128 against the fp32 MFMA
 // tiles of the same size that they replace: 4096 x 1024 x 1024 (M N K)
 // 47-51 / 73 us, was 83.7; 4096 x 1024 x 4096 158-170 / 255, was 267;
@@ -345,8 +347,10 @@ hipError_t split_go(const NodeKernel& k, hipStream_t s) {
   const bool ak = k.amode == GM_K, bk = k.bmode == GM_K;
   if (ak && bk) FLUID_FS(true, true);
   else if (ak) FLUID_FS(true, false);
-  else if (bk) FLUID_FS(false, true);
-  else FLUID_FS(false, false);
+  else if constexpr (BM == 128) {
+    if (bk) FLUID_FS(false, true);
+    else FLUID_FS(false, false);
+  } else return hipErrorInvalidValue;
 #undef FLUID_FS
   return hipGetLastError();
 }

@@ -336,6 +336,26 @@ bool row_product(const NodeKernel& k) {
   return p.K >= 512 * kept || (p.M == 1 && p.K >= 128 && p.N <= 4096);
 }
 
+// The kernel that runs an fp32 product of tile 8 or 9 (both operands of unit
+// stride): 8 the 256 x 128 split tile, 9 the 128 x 128 one, 1 the 64 x 64 fp32
+// tile.  Tile 8 asks for the larger tile, which pays where it needs clearly
+// fewer rounds of the 256 CUs (a round takes 1.7 of the smaller tile's: 4096 x
+// 1024 x 1536, M K N, 1 round and 2, 81 us and 92; 3000 x 1024 x 3000, 2 and 3,
+// 158 and 138; 4096 x 1024 x 4096, 2 and 4, 171 and 193) and A is K-contiguous
+// (otherwise it spills: 248 us).  The 128 x 128 tile fills a CU's LDS, so that
+// nothing overlaps the loads and stores of a K of one or two K-tiles: 2048 x
+// 64 x 2048 14.6 us against 13.6, 3000 x 64 x 3000 32.0 against 21.1 (at K 256
+// 23 to 144 us, where the fp32 tiles of its size took 26 to 152).
+int split_tile_of(const NodeKernel& k, int tile) {
+  const GemmParams& p = k.gemm;
+  auto rounds = [&](uint32_t tm) {
+    const uint64_t tiles = (uint64_t)((p.M + tm - 1) / tm) * ((p.N + 127) / 128) * p.G;
+    return (tiles + 255) / 256;
+  };
+  if (tile == 8 && k.amode == GM_K && 17 * rounds(256) < 10 * rounds(128)) return 8;
+  return p.K <= 64 ? 1 : 9;
+}
+
 NodeKernel prepare_gemm(const Node& nd, int variant, int dtype, const std::vector<Operand>& ins, const Operand& out) {
   NodeKernel k;
   if (packs_weight(nd.op, variant) && (nd.ins.size() != 2 || nd.ins[1] >= 0 || ins[1].shape.size() != 2)) {
@@ -451,7 +471,7 @@ NodeKernel prepare_gemm(const Node& nd, int variant, int dtype, const std::vecto
   // persistent with the whole K (at most 128) in LDS;
   // fp32 6: 16x32 with K split over 8 wavefronts, 7: 32x32 over 4, operands
   // by LDS DMA per wavefront, 8: 256x128 and 9: 128x128, bf16
-  // splits (k_gemm_f32_split.hip)
+  // splits (k_gemm_f32_split.hip; split_tile_of)
   static const uint32_t TM[] = {128, 64, 32, 32, 64, 32, 256, 128, 256, 128};
   static const uint32_t TN[] = {128, 64, 32, 32, 32, 32, 128, 128, 128, 128};
   uint32_t tm = TM[tile], tn = TN[tile];
@@ -480,6 +500,11 @@ NodeKernel prepare_gemm(const Node& nd, int variant, int dtype, const std::vecto
     k.available = false;
     k.why = "buffer-load tiles address at most 2 GiB per operand";
     return k;
+  }
+  if (tile >= 8 && f32) {
+    k.gemm_tile = split_tile_of(k, tile);
+    tm = k.gemm_tile == 8 ? 256 : k.gemm_tile == 9 ? 128 : 64;
+    tn = k.gemm_tile == 1 ? 64 : 128;
   }
   if (tile == 6 && f32 && row_product(k)) {
     k.gemm_row = true;

@@ -10,9 +10,10 @@
 //                               tiles ahead; 8: 256x128, two workgroups per
 //                               CU; 9: 128x128, whole K (<= 128) in LDS;
 //                               fp32 6: 16x32, 7: 32x32 tiles, operands by
-//                               LDS DMA per wavefront; 8: 256x128, 9:
+//                               LDS DMA per wavefront; 8: 256x128 (where the
+//                               output is large enough, else as 9), 9:
 //                               128x128, three-way bf16 splits on the bf16
-//                               matrix cores
+//                               matrix cores (K <= 64: the 64x64 tile)
 //   ADD MUL                     0: streaming elementwise in output order
 //   GELU SILU TRANSPOSE RESHAPE 0: streaming; 1: LDS-tiled (input and output
 //                               unit-stride dims differ)
