@@ -60,18 +60,14 @@ __device__ __forceinline__ TileCoord tile_coord_lin(const GemmParams& p, uint32_
 // (causal bit 1) the work of tile row tm is proportional to tm + 1, and in
 // row-major order workgroup bid, which runs on XCD bid % 8, has tile row
 // bid % 8 of its head when a head has eight: one XCD gets every long tile.
-// So: tile rows from the longest to the shortest, the heads fastest (a head
-// stays on one XCD), and every second run of 256 workgroups, one for every
-// CU, backwards, so that a CU with two of them gets a long and a short tile.
+// So, where there are tiles enough (causal bit 2, prepare_gemm): tile rows
+// from the longest to the shortest, the heads fastest (a head stays on one
+// XCD where their number is a multiple of eight), and every second run of 256
+// workgroups, one for every CU, backwards, so that a CU with two of them gets
+// a long and a short tile.
 // P V of 32 heads of 2048 x 2048, D 128, bf16 (256 tiles): 96 -> 85 us.
 __device__ __forceinline__ TileCoord tile_coord_at(const GemmParams& p, uint32_t bid, uint32_t BM, uint32_t BN) {
-  if (p.causal & 2u) {
-    const uint32_t per_m = p.tiles_n * p.G, total = p.tiles_m * per_m;
-    uint32_t i = bid;
-    if ((i & 256u) && (i | 255u) < total) i ^= 248u;  // eight by eight: bid % 8 stays
-    const uint32_t m = i / per_m, q = i - m * per_m, tn = q / p.G, g = q - tn * p.G;
-    bid = (g * p.tiles_m + (p.tiles_m - 1u - m)) * p.tiles_n + tn;
-  }
+  if (p.causal & 4u) bid = longest_first(bid, p.tiles_m, p.tiles_n, p.G);
   return tile_coord_lin(p, bid, BM, BN);
 }
 // One workgroup per tile.

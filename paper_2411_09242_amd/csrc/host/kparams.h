@@ -125,6 +125,23 @@ struct ConvParams {
   uint32_t x_bytes, w_bytes;  // tensor sizes (the bf16-split kernel: below 2 GiB)
 };
 
+#if defined(__HIP__)
+#define FLUID_HD __host__ __device__ inline
+#else
+#define FLUID_HD inline
+#endif
+
+// The row-major tile index (over G batches of tiles_m x tiles_n) of workgroup
+// bid: tile rows from the last to the first, the batches fastest, and every
+// second run of 256 workgroups backwards (eight by eight: bid % 8 stays).
+FLUID_HD uint32_t longest_first(uint32_t bid, uint32_t tiles_m, uint32_t tiles_n, uint32_t G) {
+  const uint32_t per_m = tiles_n * G, total = tiles_m * per_m;
+  uint32_t i = bid;
+  if ((i & 256u) && (i | 255u) < total) i ^= 248u;
+  const uint32_t m = i / per_m, q = i - m * per_m, tn = q / G, g = q - tn * G;
+  return (g * tiles_m + (tiles_m - 1u - m)) * tiles_n + tn;
+}
+
 // C[g, m, n] = sum_k A[g, m, k] * B[g, k, n]; g = g1 * G2 + g2 and
 // m = m1 * M2 + m2 (two-level decomposition of batch and row indices).
 struct GemmParams {
@@ -143,7 +160,8 @@ struct GemmParams {
   // Causal attention (rows m are query positions, columns or k key
   // positions): bit 0, only C[m][n] with n <= m is ever read, so tiles with
   // every n > m may be skipped; bit 1, A[m][k] = 0 for k > m, so the K loop
-  // of rows m0 .. m0 + BM - 1 may stop at m0 + BM.
+  // of rows m0 .. m0 + BM - 1 may stop at m0 + BM; bit 2 (with bit 1), the
+  // tiles are dealt by longest_first.
   uint32_t causal;
   // Epilogue: C[m][n] = act(sum_k A B + bias[n]) (rop 0), that plus R[m][n]
   // (rop 1) or times R[m][n] (rop 2); bias a dense [N] vector or none when
