@@ -221,55 +221,102 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   auto parked = [&](int g, int e) {
     return ((g * WM * WN + wpos) * (4 * NB - OWN) + (e / OWN > g ? e - OWN : e)) * 64 + lane;
   };
-#pragma unroll
-  for (int e = 0; e < 4 * NB; ++e)
-    if (e / OWN != grp) {
-      const f32x16& x = acc[e / 4 / FJ][e / 4 % FJ];
-      const int v = 4 * (e % 4);
-      red[parked(grp, e)] = make_float4(x[v], x[v + 1], x[v + 2], x[v + 3]);
-    }
-  __syncthreads();
   float out[OWN][4];
+  auto combine = [&]() {
+#pragma unroll
+    for (int e = 0; e < 4 * NB; ++e)
+      if (e / OWN != grp) {
+        const f32x16& x = acc[e / 4 / FJ][e / 4 % FJ];
+        const int v = 4 * (e % 4);
+        red[parked(grp, e)] = make_float4(x[v], x[v + 1], x[v + 2], x[v + 3]);
+      }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 4 * NB; ++e)
+      if (e / OWN == grp) {
+        const f32x16& x = acc[e / 4 / FJ][e / 4 % FJ];
+        float* y = out[e % OWN];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) y[t] = x[4 * (e % 4) + t];
+#pragma unroll
+        for (int g = 0; g < KS; ++g)
+          if (g != grp) {
+            const float4 z = red[parked(g, e)];
+            y[0] += z.x, y[1] += z.y, y[2] += z.z, y[3] += z.w;
+          }
+      }
+  };
+  combine();
   bool bad = false;
 #pragma unroll
-  for (int e = 0; e < 4 * NB; ++e)
-    if (e / OWN == grp) {
-      const f32x16& x = acc[e / 4 / FJ][e / 4 % FJ];
-      float* y = out[e % OWN];
+  for (int e = 0; e < OWN; ++e)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) y[t] = x[4 * (e % 4) + t];
-#pragma unroll
-      for (int g = 0; g < KS; ++g)
-        if (g != grp) {
-          const float4 z = red[parked(g, e)];
-          y[0] += z.x, y[1] += z.y, y[2] += z.z, y[3] += z.w;
-        }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) bad |= !(fabsf(y[t]) <= 3.4028234663852886e38f);
-    }
+    for (int t = 0; t < 4; ++t) bad |= !(fabsf(out[e][t]) <= 3.4028234663852886e38f);
   if (__syncthreads_or(bad)) {
-    // the exceptions of the split: the blocks again, with the fp32 MFMA
+    // the exceptions of the split: the tile again with the fp32 MFMA, the
+    // groups taking KS runs of K.  Step t of sixteen k takes, in the k slot
+    // lane / 32, the real k 8 (lane / 32) + t of both operands; the next
+    // sixteen k are in flight.
+    const uint32_t kg = (p.K + 16u * KS - 1u) / (16u * KS) * 16u;
+    const uint32_t kb = (uint32_t)grp * kg, ke = min(p.K, kb + kg);
+    uint32_t ao[FI], bo[FJ];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      if (4 * b / OWN > grp || (4 * b + 3) / OWN < grp) continue;
-      const uint32_t m = m0 + wm * 32 * FI + 32 * (b / FJ) + lr, o = n0 + wn * 32 * FJ + 32 * (b % FJ) + lr;
-      const uint32_t ao = 4u * (uint32_t)(m < p.M ? conv_row_off(p, m, p.x_n, p.x_h, p.x_w) : 0);
-      const uint32_t bo = 4u * ((o < p.Co ? o : 0) * p.K);
-      f32x16 x;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) x[v] = 0.f;
-      for (uint32_t k = lh; k < p.K + lh; k += 2) {
-        const uint32_t c = fdiv(k, p.khw_div), r = k - c * p.KHW, u = fdiv(r, p.kw_div), v = r - u * p.KW;
-        const int32_t co = (int32_t)c * p.x_c + (int32_t)u * p.x_h + (int32_t)v * p.x_w;
-        x = __builtin_amdgcn_mfma_f32_32x32x2f32(bload4(rx, k < p.K ? ao + 4u * (uint32_t)co : kOOB),
-                                                 bload4(rw, k < p.K ? bo + 4u * k : kOOB), x, 0, 0, 0);
-      }
-#pragma unroll
-      for (int e = 4 * b; e < 4 * b + 4; ++e)
-        if (e / OWN == grp)
-#pragma unroll
-          for (int t = 0; t < 4; ++t) out[e % OWN][t] = x[4 * (e % 4) + t];
+    for (int i = 0; i < FI; ++i) {
+      const uint32_t m = m0 + wm * 32 * FI + 32 * i + lr;
+      ao[i] = 4u * (uint32_t)(m < p.M ? conv_row_off(p, m, p.x_n, p.x_h, p.x_w) : 0);
     }
+#pragma unroll
+    for (int j = 0; j < FJ; ++j) {
+      const uint32_t o = n0 + wn * 32 * FJ + 32 * j + lr;
+      bo[j] = 4u * ((o < p.Co ? o : 0) * p.K);
+    }
+    struct Octs {
+      float a[FI][8], b[FJ][8];
+    };
+    auto octs = [&](Octs& O, uint32_t k1) {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const uint32_t k = k1 + t;
+        const uint32_t c = fdiv(k, p.khw_div), r = k - c * p.KHW, u = fdiv(r, p.kw_div), v = r - u * p.KW;
+        const uint32_t co = 4u * (uint32_t)((int32_t)c * p.x_c + (int32_t)u * p.x_h + (int32_t)v * p.x_w);
+#pragma unroll
+        for (int i = 0; i < FI; ++i) O.a[i][t] = bload4(rx, k < ke ? ao[i] + co : kOOB);
+        if constexpr (!WV) {
+#pragma unroll
+          for (int j = 0; j < FJ; ++j) O.b[j][t] = bload4(rw, k < ke ? bo[j] + 4u * k : kOOB);
+        }
+      }
+      if constexpr (WV) {
+#pragma unroll
+        for (int j = 0; j < FJ; ++j)
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const uint4 w = bload16(rw, k1 + 4 * h < ke ? bo[j] + 4u * (k1 + 4 * h) : kOOB);
+            O.b[j][4 * h] = __uint_as_float(w.x), O.b[j][4 * h + 1] = __uint_as_float(w.y);
+            O.b[j][4 * h + 2] = __uint_as_float(w.z), O.b[j][4 * h + 3] = __uint_as_float(w.w);
+          }
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < FI; ++i)
+#pragma unroll
+      for (int j = 0; j < FJ; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    Octs nx;
+    octs(nx, kb + 8 * lh);
+    for (uint32_t k0 = kb; k0 < ke; k0 += 16) {
+      const Octs O = nx;
+      octs(nx, k0 + 16 + 8 * lh);
+#pragma unroll
+      for (int t = 0; t < 8; ++t)
+#pragma unroll
+        for (int i = 0; i < FI; ++i)
+#pragma unroll
+          for (int j = 0; j < FJ; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(O.a[i][t], O.b[j][t], acc[i][j], 0, 0, 0);
+    }
+    combine();
   }
 
 #pragma unroll
