@@ -5,13 +5,14 @@
 //
 //   y[n, o, i, j] = sum_{c, u, v} x[n, c, i+u, j+v] * w[o, c, u, v] + b[o]
 //
-// Rows m = (n, i, j) are output pixels, columns output channels o, the
-// reduction runs over k = (c, u, v), the weight's own order.  In any layout
-// x[n, c, i+u, j+v] sits at row_offset(m) + col_offset(k), so the unfolded
-// input is never built.  The lanes of a wavefront load 64 consecutive pixels
-// of one k (coalesced when W is the input's unit-stride dim), k and its
-// offset in scalar registers; a lane's eight k of one pixel are one 16-byte
-// LDS write per bf16 plane.  The weight rows are K-contiguous.
+// Rows m are output pixels, (n, i, j), or (n, j, i) where H is the input's
+// unit-stride dim (512 -> 512 at 14 x 14 126 -> 68 us in that layout), columns
+// output channels o, the reduction runs over k = (c, u, v), the weight's own
+// order.  In any layout x[n, c, i+u, j+v] sits at row_offset(m) +
+// col_offset(k), so the unfolded input is never built.  The lanes of a
+// wavefront load 64 consecutive pixels of one k, k and its offset in scalar
+// registers; a lane's eight k of one pixel are one 16-byte LDS write per bf16
+// plane.  The weight rows are K-contiguous.
 //
 // BM x BN tile, eight wavefronts as KS groups of WM x WN, group s taking the
 // s-th 16 k of every K-tile of 16 KS (partial sums added in group order):
@@ -35,12 +36,13 @@ namespace fluid {
 
 namespace {
 
-__device__ __forceinline__ int32_t conv_row_off(const ConvParams& p, uint32_t m, int32_t sn, int32_t sh, int32_t sw) {
+// Offset of row m, strides of the batch, the outer and the inner pixel dim.
+__device__ __forceinline__ int32_t conv_row_off(const ConvParams& p, uint32_t m, int32_t sn, int32_t so, int32_t si) {
   const uint32_t n = fdiv(m, p.ohw_div);
   const uint32_t r = m - n * p.OHW;
-  const uint32_t i = fdiv(r, p.ow_div);
-  const uint32_t j = r - i * p.OW;
-  return (int32_t)n * sn + (int32_t)i * sh + (int32_t)j * sw;
+  const uint32_t i = fdiv(r, p.pi_div);
+  const uint32_t j = r - i * p.PI;
+  return (int32_t)n * sn + (int32_t)i * so + (int32_t)j * si;
 }
 
 }  // namespace
@@ -79,7 +81,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int c = q * T + tid;
     const int row = c % BM, kc = __builtin_amdgcn_readfirstlane(c / BM);
     const uint32_t m = m0 + row;
-    a_off[q] = 4u * (uint32_t)(m < p.M ? conv_row_off(p, m, p.x_n, p.x_h, p.x_w) : 0);
+    a_off[q] = 4u * (uint32_t)(m < p.M ? conv_row_off(p, m, p.x_n, p.x_po, p.x_pi) : 0);
     a_k[q] = 8 * kc;
     a_lds[q] = row * BK * 2 + ((kc ^ split_swz<BK>(row)) << 4);
   }
@@ -263,7 +265,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int i = 0; i < FI; ++i) {
       const uint32_t m = m0 + wm * 32 * FI + 32 * i + lr;
-      ao[i] = 4u * (uint32_t)(m < p.M ? conv_row_off(p, m, p.x_n, p.x_h, p.x_w) : 0);
+      ao[i] = 4u * (uint32_t)(m < p.M ? conv_row_off(p, m, p.x_n, p.x_po, p.x_pi) : 0);
     }
 #pragma unroll
     for (int j = 0; j < FJ; ++j) {
@@ -328,7 +330,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const uint32_t m = m0 + wm * 32 * FI + 32 * (e / 4 / FJ) + 8 * (e % 4) + 4 * lh + t;
-      if (m < p.M) p.y[conv_row_off(p, m, p.y_n, p.y_h, p.y_w) + (int32_t)o * p.y_c] = out[e % OWN][t] + bo;
+      if (m < p.M) p.y[conv_row_off(p, m, p.y_n, p.y_po, p.y_pi) + (int32_t)o * p.y_c] = out[e % OWN][t] + bo;
     }
   }
 }

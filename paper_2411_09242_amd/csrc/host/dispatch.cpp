@@ -607,6 +607,13 @@ NodeKernel prepare_conv(const Node& nd, int variant, int dtype, const std::vecto
   const bool split = variant % 2 == 0 && xb < 0x7fffffff && wb < 0x7fffffff;
   p.x_bytes = (uint32_t)std::min<int64_t>(xb, 0x7fffffff);
   p.w_bytes = (uint32_t)std::min<int64_t>(wb, 0x7fffffff);
+  const bool h_inner = p.x_h == 1 && p.x_w != 1;
+  p.PI = h_inner ? OH : OW;
+  p.pi_div = make_fastdiv(p.PI);
+  p.x_po = h_inner ? p.x_w : p.x_h;
+  p.x_pi = h_inner ? p.x_h : p.x_w;
+  p.y_po = h_inner ? p.y_w : p.y_h;
+  p.y_pi = h_inner ? p.y_h : p.y_w;
   k.conv_kord = split ? 0 : 1;
   k.conv_tile = variant >= 4 ? 32 : 64;
   if (split) {

@@ -122,7 +122,13 @@ struct ConvParams {
   int32_t x_n, x_c, x_h, x_w;
   int32_t y_n, y_c, y_h, y_w;
   uint32_t tiles_n;
-  uint32_t x_bytes, w_bytes;  // tensor sizes (the bf16-split kernel: below 2 GiB)
+  // the bf16-split kernel: tensor sizes (below 2 GiB); its rows m, pixels with
+  // the dim of unit stride in x innermost (i where that is H, else j): the
+  // inner extent and the strides of the outer and the inner pixel dim
+  uint32_t x_bytes, w_bytes;
+  uint32_t PI;
+  FastDiv pi_div;
+  int32_t x_po, x_pi, y_po, y_pi;
 };
 
 #if defined(__HIP__)

@@ -229,3 +229,45 @@ def test_split_convolution_operand_sizes(sizes, variant):
     say("conv sizes", sizes, variant)
     got = convolution(variant, x, w, np.zeros(33, np.float32))
     assert (np.abs(got - exact(x, w)) <= bound).all()
+
+
+@pytest.mark.parametrize("dist", ["normal", "positive", "wide"])
+def test_split_convolution_error(dist):
+    """The root mean square of the errors against 64-bit arithmetic, in units
+    of sum |x w|, no larger than the fp32 MFMA kernel's."""
+    from numpy.lib.stride_tricks import sliding_window_view
+    rng = np.random.default_rng(11)
+    x, w = rng.standard_normal((1, 96, 18, 18)), 0.05 * rng.standard_normal((72, 96, 3, 3))
+    if dist == "positive":
+        x = np.maximum(x, 0.0)
+    elif dist == "wide":
+        x, w = x * np.exp(4 * rng.standard_normal(x.shape)), w * np.exp(4 * rng.standard_normal(w.shape))
+    x, w = x.astype(np.float32), w.astype(np.float32)
+
+    def exact(x, w):
+        win = sliding_window_view(x.astype(np.float64), (3, 3), axis=(2, 3))
+        return np.tensordot(win, w.astype(np.float64), ([1, 4, 5], [1, 2, 3])).transpose(0, 3, 1, 2)
+
+    ref, size = exact(x, w), exact(np.abs(x), np.abs(w))
+    rms = {}
+    for v in (0, 1, 2, 4):
+        e = (convolution(v, x, w, np.zeros(72, np.float32)) - ref) / size
+        rms[v] = float(np.sqrt((e * e).mean()))
+    say("conv error", dist, rms)
+    assert all(rms[v] <= rms[1] for v in (0, 2, 4))
+
+
+@pytest.mark.parametrize("variant", [0, 2, 4])
+@pytest.mark.parametrize("case", [((2, 5, 12, 8), (9, 5, 2, 4)), ((1, 6, 7, 40), (35, 6, 3, 1)), ((3, 4, 70, 3), (33, 4, 3, 3))],
+                         ids=str)
+def test_split_convolution_layouts(case, variant, tmp_path):
+    """Rows of pixels along W and, for inputs contiguous along H, along H: tall
+    and wide images, several of them, kernels that are not square."""
+    from test_gpu_conv import _check, conv_graph
+    og, a, c = conv_graph(*case, True)
+    L = set(map(tuple, layouts.layout_list(case[0]))), set(map(tuple, layouts.layout_list(og.edge_shape(c))))
+    for pa in ((0, 1, 2, 3), (0, 1, 3, 2), (0, 3, 1, 2), (1, 3, 0, 2), (3, 0, 1, 2), (0, 2, 3, 1)):
+        for pc in ((0, 1, 2, 3), (0, 1, 3, 2), (0, 2, 3, 1)):
+            if pa in L[0] and pc in L[1]:
+                say(f"split conv {case} v{variant} x{pa} y{pc}")
+                _check(og, {a: pa, c: pc}, {og.producer(c): variant}, tmp_path, sum(case[0]))
