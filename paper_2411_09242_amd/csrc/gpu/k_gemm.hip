@@ -734,12 +734,7 @@ hipError_t launch_gemm(const NodeKernel& k, hipStream_t s) {
   if (k.gemm_tile >= 8 && k.dtype == DT_F32) return launch_gemm_f32_split(k, s);
   if (k.gemm_row) return launch_gemv_f32(k, s);
   if (k.gemm_tile >= 6) return k.dtype == DT_BF16 ? launch_gemm_bf16_pipe(k, s) : launch_gemm_f32_dl(k, s);
-  // bf16, both operands K-contiguous and below 2 GiB (buffer loads): the DMA
-  // kernel, faster at every size measured from 16 x 1024 x 1024 on (4.8
-  // against 7.6 us; 3.4 against 3.6 at 37 x 96 x 72)
-  if (k.gemm_tile >= 2 && k.gemm_tile <= 4 && k.dtype == DT_BF16 && k.amode == GM_K && k.bmode == GM_K &&
-      p.a_bytes < 0x7fffffffu && p.b_bytes < 0x7fffffffu)
-    return launch_gemm_bf16_skd(k, s);
+  if (k.gemm_dma) return launch_gemm_bf16_skd(k, s);
   if (k.gemm_tile >= 2) return k.dtype == DT_BF16 ? gemm_sk_dispatch<uint16_t>(k, s) : gemm_sk_dispatch<float>(k, s);
   return k.gemm_tile == 0 ? gemm_a<128>(k, s) : gemm_a<64>(k, s);
 }

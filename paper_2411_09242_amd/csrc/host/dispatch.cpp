@@ -501,6 +501,10 @@ NodeKernel prepare_gemm(const Node& nd, int variant, int dtype, const std::vecto
     k.why = "buffer-load tiles address at most 2 GiB per operand";
     return k;
   }
+  // bf16, both operands K-contiguous and below 2 GiB (buffer loads): the DMA
+  // kernel, faster at every size measured from 16 x 1024 x 1024 on (4.8
+  // against 7.6 us; 3.4 against 3.6 at 37 x 96 x 72)
+  k.gemm_dma = tile >= 2 && tile <= 4 && !f32 && k.amode == GM_K && k.bmode == GM_K && sa < 0x7fffffff && sb < 0x7fffffff;
   if (tile >= 8 && f32) {
     k.gemm_tile = split_tile_of(k, tile);
     tm = k.gemm_tile == 8 ? 256 : k.gemm_tile == 9 ? 128 : 64;
@@ -704,7 +708,11 @@ std::string NodeKernel::name() const {
       };
       static const char* tiles[] = {"t128", "t64", "sk32w4", "sk32w8", "sk64x32w4", "sk32w16", "p256x128", "p128", "p256x128s3", "q128"};
       static const char* tiles_f32[] = {"t128", "t64", "sk32w4", "sk32w8", "sk64x32w4", "sk32w16", "dl16x32w8", "dl32w4", "s256x128", "s128"};
-      return "gemm_" + dt + "_" + (gemm_row ? "row4" : (dtype == DT_BF16 ? tiles : tiles_f32)[gemm_tile]) + "_a" + gm[amode] + "_b" + gm[bmode] + "_c" +
+      static const char* tiles_dma[] = {"dma32w4", "dma32w8", "dma64x32w4"};  // tiles 2 to 4
+      const char* tile = gemm_row   ? "row4"
+                         : gemm_dma ? tiles_dma[gemm_tile - 2]
+                                    : (dtype == DT_BF16 ? tiles : tiles_f32)[gemm_tile];
+      return "gemm_" + dt + "_" + tile + "_a" + gm[amode] + "_b" + gm[bmode] + "_c" +
              (cmode == 1 ? "n" : cmode == 2 ? "m" : "g") + (gemm.causal ? "_causal" + std::to_string(gemm.causal & 3u) : "") +
              epi_suffix();
     }

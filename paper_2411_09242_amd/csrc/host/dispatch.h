@@ -59,6 +59,7 @@ struct NodeKernel {
   bool red_block = false;       // row reduction: one 256-thread workgroup per row (variant 2)
   int gemm_tile = 0, amode = 0, bmode = 0, cmode = 0;  // cmode 0 generic, 1 N-contig, 2 M-contig
   bool gemm_row = false;        // fp32 tile 6 on at most four rows: the row-times-matrix kernel
+  bool gemm_dma = false;        // bf16 tiles 2 to 4 on K-contiguous operands: the LDS DMA kernel
   std::string name() const;
 };
 

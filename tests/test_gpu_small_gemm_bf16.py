@@ -23,4 +23,5 @@ def test_group_counts(K, rows, variant, tmp_path):
     for pc in layouts.layout_list((B, S, 36)):
         say(f"small bf16 gemm K {K} {rows} v{variant} C{pc}")
         lp = _check_gemm(og, {c: pc}, {1: variant}, tmp_path, K, "bf16")
-        assert lp.kernel(1).startswith("gemm_bf16_sk") and "_ak_bk_" in lp.kernel(1)
+        tile = {12: "dma32w4", 13: "dma32w8", 14: "dma64x32w4"}[variant]
+        assert lp.kernel(1).startswith(f"gemm_bf16_{tile}_ak_bk_")
