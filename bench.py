@@ -33,6 +33,15 @@ sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0
 PEAK_TFLOPS = {"f32": 157.3, "bf16": 2516.6}
+# fp32 products summed from six bf16 ones on the bf16 matrix cores (launch
+# names gemm_f32_s<tile>, conv_f32_s<tile>)
+PEAK_SPLIT_TFLOPS = round(PEAK_TFLOPS["bf16"] / 6, 1)
+
+
+def peak_tflops(launch_name, dtype):
+    """The matrix peak of the unit that the launch's kernel runs on."""
+    import re
+    return PEAK_SPLIT_TFLOPS if re.match(r"(gemm|conv)_f32_s\d", launch_name) else PEAK_TFLOPS[dtype]
 
 # HBM bytes per launch of each workload's dominant launch: two rocprofv3
 # --pmc passes (FETCH_SIZE, then WRITE_SIZE) over `bench.py --kernel-only`
@@ -269,7 +278,8 @@ def op_class_rates(g, units, ex, steps, torch):
         work = sum(u["work"] for u in us)
         if us[0]["kind"] == "flop":
             rate = work / (ms_c * 1e-3) / 1e12
-            peak, unit = PEAK_TFLOPS[g.dtype], "TFLOP/s"
+            # the class's peak rate: its work at each launch's own peak
+            peak, unit = work / sum(u["work"] / peak_tflops(u["name"], g.dtype) for u in us), "TFLOP/s"
         else:
             rate = work / (ms_c * 1e-3) / 1e9
             peak, unit = PEAK_HBM_GBS, "GB/s"
@@ -469,7 +479,7 @@ def measure_workload(F, torch, cfg, x, consts, steps, warmup, reps, save_table=N
     # or bytes / HBM peak) -- fixed by the graph and the plan, not by timing
     # noise or by the per-dispatch overhead a tracer adds
     def ideal_ms(us):
-        peak = (PEAK_TFLOPS[g.dtype] * 1e12) if us[0]["kind"] == "flop" else (PEAK_HBM_GBS * 1e9)
+        peak = (peak_tflops(us[0]["name"], g.dtype) * 1e12) if us[0]["kind"] == "flop" else (PEAK_HBM_GBS * 1e9)
         return sum(u["work"] for u in us) / peak
     dom_key = max(by_sig, key=lambda k: (ideal_ms(by_sig[k]), -by_sig[k][0]["index"]))
     dom = by_sig[dom_key]
@@ -526,7 +536,7 @@ def measure_workload(F, torch, cfg, x, consts, steps, warmup, reps, save_table=N
     traffic = entry[0] if entry and entry[1] == kernel_source_hash(dom[0]["name"]) else None
     if kind == "flop":
         achieved = work / (avg_ms * 1e-3) / 1e12
-        peak = PEAK_TFLOPS[g.dtype]
+        peak = peak_tflops(dom[0]["name"], g.dtype)
         roof = {"bound": "mfma", "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
                 "frac": round(achieved / peak, 4), "traffic": traffic}
     else:
