@@ -21,12 +21,13 @@
 //   64 x 32, KS 8 (64 x 32): layers with fewer tiles than compute units,
 //   where a tile's K-tiles must be few.
 // Measured against the fp32 MFMA kernel's best (3 x 3, C -> Co at H x W):
-// 64 -> 64 at 224 72 -> 54 us, 128 -> 128 at 112 76 -> 46 (128 x 64); 256 ->
-// 256 at 56 77 -> 50, 128 -> 256 43 -> 29 (64 x 64); 512 -> 512 at 28 122 ->
-// 66, 256 -> 512 65 -> 37 (64 x 32); at 14 x 14 (64 tiles) both take 63-65.
-// At 56 x 56 the matrix cores are busy a quarter of the time: the split
-// (VALU a third), its LDS writes and reads (a third) and the MFMAs share
-// a barrier per K-tile and overlap little.  Tried, slower: two and three
+// 64 -> 64 at 224 72 -> 56 us, 128 -> 128 at 112 76 -> 48 (128 x 64); 256 ->
+// 256 at 56 77 -> 53, 128 -> 256 43 -> 31 (64 x 64); 512 -> 512 at 28 121 ->
+// 67, 256 -> 512 65 -> 38 (64 x 32); at 14 x 14 (64 tiles) both take 63-66.
+// For three input channels the fp32 kernels are faster (64 at 224 x 224: 17
+// and 29 us).  At 56 x 56 the matrix cores are busy 23% of the time, VALU 44%,
+// LDS 30%: the split, its LDS writes and reads and the MFMAs share a barrier
+// per K-tile and overlap little.  Tried, slower: two and three
 // register sets ahead, MFMAs interleaved with the split by scheduling
 // groups; no faster: (c, u, v) stepped in scalar registers.
 #include "launch.h"
@@ -132,23 +133,14 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     }
   };
-  auto put = [&](const float* v, uint8_t* dst, int plane) {
-    uint32_t h[4], m[4], l[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) split2(v[2 * i], v[2 * i + 1], h[i], m[i], l[i]);
-    *(uint4*)dst = make_uint4(h[0], h[1], h[2], h[3]);
-    *(uint4*)(dst + plane) = make_uint4(m[0], m[1], m[2], m[3]);
-    *(uint4*)(dst + 2 * plane) = make_uint4(l[0], l[1], l[2], l[3]);
-  };
   auto lstore = [&](const Regs& R, int st) {
     uint8_t* s = lds + st * STAGE;
 #pragma unroll
-    for (int q = 0; q < NA; ++q) put(R.a[q], s + a_lds[q], APL);
+    for (int q = 0; q < NA; ++q) split_put(R.a[q], s + a_lds[q], APL);
 #pragma unroll
-    for (int q = 0; q < NBL; ++q) put(R.b[q], s + b_lds[q], BPL);
+    for (int q = 0; q < NBL; ++q) split_put(R.b[q], s + b_lds[q], BPL);
   };
 
-  // acc: the leading products; low: the five others (k_gemm_f32_split.hip)
   f32x16 acc[FI][FJ], low[FI][FJ];
 #pragma unroll
   for (int i = 0; i < FI; ++i)
@@ -178,21 +170,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       for (int j = 0; j < FJ; ++j) b[pl][j] = *(const bf16x8*)(s + b_rd[j] + pl * BPL);
     }
   };
-  auto mul = [&]() {
-    constexpr int PA[5] = {0, 1, 1, 0, 2}, PB[5] = {1, 0, 1, 2, 0};
-#pragma unroll
-    for (int t = 4; t >= 0; --t)
-#pragma unroll
-      for (int i = 0; i < FI; ++i)
-#pragma unroll
-        for (int j = 0; j < FJ; ++j)
-          low[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[t]][i], b[PB[t]][j], low[i][j], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < FI; ++i)
-#pragma unroll
-      for (int j = 0; j < FJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][i], b[0][j], acc[i][j], 0, 0, 0);
-  };
 
   // K-tile t is multiplied from stage t % 2 while tile t+1, loaded into
   // registers during tile t-1, is split into the other stage and tile t+2
@@ -207,7 +184,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     fread(t & 1);
     lstore(R, (t + 1) & 1);
     gload(R, (t + 2) * BK);
-    mul();
+    split_mul(a, b, acc, low);
     __syncthreads();
   }
 #pragma unroll

@@ -9,16 +9,16 @@
 //    does not depend on timing);
 //  * both operands go to LDS by DMA (`buffer_load ... lds`, 16 bytes per
 //    lane), each wavefront into stages of its own (no barrier in the loop),
-//    three 16-k groups in flight; a CU takes 128 GB/s from L2 by DMA and 73
-//    into registers, 37 where the loads touch 64-byte row pieces, as a
-//    K-contiguous operand's do.  Nothing is loaded past the slice: it would
-//    cost as much issue time as a real load.
+//    three 16-k groups in flight; a K-contiguous operand comes in 64-byte row
+//    pieces, half a line.  Nothing is loaded past the slice: it would cost as
+//    much issue time as a real load.
 //
 // Measured (M K N, weights from HBM; before: loads straight into registers):
 // 128 x 3072 x 768 15.8 -> 13.3 us, 128 x 768 x 3072 on a K-contiguous weight
 // 17.1 -> 14.2, 512 x 3072 x 768 38.4 -> 31.0 (16 x 32); 512 x 768 x 3072
 // 33.8 -> 29.4 (32 x 32).  What bounds it: at 128 x 3072 x 768 the DMA alone
-// takes 12.5 us and the LDS reads and MFMAs alone 11.6, 1.7 of each the launch.
+// takes 12.5 us and the LDS reads and MFMAs alone 11.6, 1.7 of each the launch
+// (113 MB in 10.8 us, 55 GB/s for each of the 192 workgroups).
 // Three stages, so that two or three workgroups share a CU, against six:
 // 13.3 and 14.3 us there, 36.8 and 56 at 512 x 768 x 3072; sixteen
 // wavefronts, a K order rotated by tile row and XCD-contiguous tile columns

@@ -57,12 +57,12 @@ __device__ __forceinline__ TileCoord split_tile(const GemmParams& p, uint32_t BM
 //    over K rather than 64 x 32 wavefront tiles, which would read LDS half as
 //    much again per MFMA.
 //  Which of them runs: split_tile_of in dispatch.cpp.
-// Measured (weights from HBM), 128 x 128 / 256 x 128 against the fp32 MFMA
-// tiles of the same size that they replace: 4096 x 1024 x 1024 (M N K)
-// 47-51 / 73 us, was 83.7; 4096 x 1024 x 4096 158-170 / 255, was 267;
-// 4096 x 4096 x 1024 184 / 167 us (206 TFLOP/s, 1.24 PFLOP/s of bf16 MFMA),
-// was 276.  Bound: 128 x 128 keeps the matrix cores 54% busy, LDS 54%, VALU
-// 40%, at the 1.9 GHz that the card's power leaves.  Tried: the groups in
+// Measured (weights from HBM) against the fp32 MFMA tiles of the same size that
+// they replace: 128 x 128 at 4096 x 1024 x 1024 (M N K) 49-52 us, was 83.7, and
+// 4096 x 1024 x 4096 164-173, was 267; 256 x 128 at 4096 x 4096 x 1024 167 us
+// (206 TFLOP/s, 1.23 PFLOP/s of bf16 MFMA), was 276.  Bound: at those sizes
+// the matrix cores are busy 62% and 59% of the time, VALU 50 and 45%, LDS 47
+// and 41% (a third of that bank conflicts).  Tried: the groups in
 // alternating MFMA and split phases (two barriers per K-tile) 8% slower; a
 // second register set, loads two K-tiles ahead, 0 to 10% slower; the six
 // products in one accumulator as fast, but with 2.6 times the error.
@@ -145,24 +145,14 @@ void gemm_f32_split_kernel(GemmParams p) {
     for (int q = 0; q < NBL; ++q)
       chunk(rb, R.b[q], b_off[q] + (int32_t)k0 * (BKC ? 1 : p.b_k), k0 + b_k[q], BKC, p.b_k);
   };
-  auto put = [&](const float* v, uint8_t* dst, int plane) {
-    uint32_t h[4], m[4], l[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) split2(v[2 * i], v[2 * i + 1], h[i], m[i], l[i]);
-    *(uint4*)dst = make_uint4(h[0], h[1], h[2], h[3]);
-    *(uint4*)(dst + plane) = make_uint4(m[0], m[1], m[2], m[3]);
-    *(uint4*)(dst + 2 * plane) = make_uint4(l[0], l[1], l[2], l[3]);
-  };
   auto lstore = [&](const Regs& R, int st) {
     uint8_t* s = lds + st * STAGE;
 #pragma unroll
-    for (int q = 0; q < NA; ++q) put(R.a[q], s + a_lds[q], APL);
+    for (int q = 0; q < NA; ++q) split_put(R.a[q], s + a_lds[q], APL);
 #pragma unroll
-    for (int q = 0; q < NBL; ++q) put(R.b[q], s + b_lds[q], BPL);
+    for (int q = 0; q < NBL; ++q) split_put(R.b[q], s + b_lds[q], BPL);
   };
 
-  // acc: the leading products h h'; low: the five others, 2^-8 smaller, so
-  // that they cost the large sums no roundings
   f32x16 acc[FI][FJ], low[FI][FJ];
 #pragma unroll
   for (int i = 0; i < FI; ++i)
@@ -197,21 +187,6 @@ void gemm_f32_split_kernel(GemmParams p) {
       for (int j = 0; j < FJ; ++j) F.b[pl][j] = *(const bf16x8*)(s + (b_rd[j] ^ (sx << 5)) + pl * BPL);
     }
   };
-  auto mul = [&](const Frag& F) {
-    constexpr int PA[5] = {0, 1, 1, 0, 2}, PB[5] = {1, 0, 1, 2, 0};
-#pragma unroll
-    for (int t = 4; t >= 0; --t)
-#pragma unroll
-      for (int i = 0; i < FI; ++i)
-#pragma unroll
-        for (int j = 0; j < FJ; ++j)
-          low[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.a[PA[t]][i], F.b[PB[t]][j], low[i][j], 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < FI; ++i)
-#pragma unroll
-      for (int j = 0; j < FJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.a[0][i], F.b[0][j], acc[i][j], 0, 0, 0);
-  };
 
   // K-tile t is multiplied from stage t % 2 while tile t+1, loaded into
   // registers during tile t-1, is split into the other stage and tile t+2
@@ -229,10 +204,10 @@ void gemm_f32_split_kernel(GemmParams p) {
     fread(F, U, 0);                                                                  \
     lstore(R, 1 - U);                                                                \
     gload(R, (t + U + 2) * BK);                                                      \
-    mul(F);                                                                          \
+    split_mul(F.a, F.b, acc, low);                                                   \
     if constexpr (ST == 2) {                                                         \
       fread(F, U, 1);                                                                \
-      mul(F);                                                                        \
+      split_mul(F.a, F.b, acc, low);                                                 \
     } else {                                                                         \
       _Pragma("unroll") for (int z = 0; z < 6 * NB; ++z) {                           \
         __builtin_amdgcn_sched_group_barrier(8, 1, 0); /* an MFMA, then */           \
