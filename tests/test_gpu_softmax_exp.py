@@ -31,11 +31,9 @@ def softmax(variant, x, tmp_path):
     return y.double().cpu().numpy()
 
 
-@pytest.mark.parametrize("row", [2048, 1001, 9000])
-@pytest.mark.parametrize("variant", [0, 1, 2])
+# the row variants hold 4096 values, the workgroup-per-row one 16-byte pieces
+@pytest.mark.parametrize("variant,row", [(0, 2048), (0, 1001), (1, 2048), (1, 1001), (1, 9000), (2, 2048)])
 def test_softmax_exponential(row, variant, tmp_path):
-    if variant != 1 and row > 4096 or variant == 2 and row % 8:
-        pytest.skip("the row variants hold 4096 values, the workgroup-per-row one 16-byte pieces")
     rng = np.random.default_rng(row)
     x = numerics.round_bf16(rng.uniform(-80.0, -60.0, (1, 400, row)))
     # a maximum of its own per row: some 20000 distinct differences
