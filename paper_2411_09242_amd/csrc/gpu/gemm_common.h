@@ -66,8 +66,14 @@ __device__ __forceinline__ TileCoord tile_coord_lin(const GemmParams& p, uint32_
 // workgroups, one for every CU, backwards, so that a CU with two of them gets
 // a long and a short tile.
 // P V of 32 heads of 2048 x 2048, D 128, bf16 (256 tiles): 96 -> 85 us.
+// The order is asked for inside the test of bit 1 and out of line: a product
+// that is not causal branches once, here and for its K limit.  Twelve layers
+// of BERT-base's sizes at 128 tokens, 60 such launches: 823 us; with bit 2
+// tested by itself, 830.
 __device__ __forceinline__ TileCoord tile_coord_at(const GemmParams& p, uint32_t bid, uint32_t BM, uint32_t BN) {
-  if (p.causal & 4u) bid = longest_first(bid, p.tiles_m, p.tiles_n, p.G);
+  if (__builtin_expect((p.causal & 2u) != 0, 0)) {
+    if (p.causal & 4u) bid = longest_first(bid, p.tiles_m, p.tiles_n, p.G);
+  }
   return tile_coord_lin(p, bid, BM, BN);
 }
 // One workgroup per tile.
